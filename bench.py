@@ -48,19 +48,19 @@ HBM_PEAK_GBS = 8000.0
 TRAFFIC_SOURCES = ("paper_2103_11847_amd/csrc/fused.hip", "paper_2103_11847_amd/csrc/mfma.h",
                    "paper_2103_11847_amd/csrc/internal.h")
 TRAFFIC = {"digest": "a44b9d1d32ecbf2c", "gemm": "f32",
-           "bytes": {"fused_fwd": 6677688, "fused_adj": 6637664}}
+           "bytes": {"fused_fwd": 6677687, "fused_adj": 6637643}}
 
 
 # The same for the O(p log p) tube transform at 512 x 512 positions, p = 256, FP32 (bytes per launch).
 LONGTUBE_SOURCES = ("paper_2103_11847_amd/csrc/fastdct.hip", "paper_2103_11847_amd/csrc/fastdct.h")
-LONGTUBE_TRAFFIC = {"digest": "2b4748b4b2668618", "bytes": 656636507}
+LONGTUBE_TRAFFIC = {"digest": "2b4748b4b2668618", "bytes": 656488202}
 
 # The same for the slice GEMMs and the paired transforms of the 512 x 512 x 64 solve
 # (bytes per launch, keyed "gemm type/kernel"), from the counter passes of the hyper512 bench.
 HYPER_TRAFFIC_SOURCES = ("paper_2103_11847_amd/csrc/gemm.hip", "paper_2103_11847_amd/csrc/transform.hip",
                          "paper_2103_11847_amd/csrc/mfma.h", "paper_2103_11847_amd/csrc/internal.h")
-HYPER_TRAFFIC = {"digest": "50678c7cb80bf0dd",
-                 "bytes": {"f32/gemm": 202097938, "f32/tube_pair": 268908161, "bf16/gemm": 134564564, "bf16/tube_pair": 235377510}}
+HYPER_TRAFFIC = {"digest": "ffd126a7e3d53253",
+                 "bytes": {"f32/gemm": 201741867, "f32/tube_pair": 268907950, "bf16/gemm": 134554572, "bf16/tube_pair": 235381035}}
 
 
 def source_digest(files):
@@ -81,7 +81,14 @@ def measured_traffic(kind, gemm):
     if h.hexdigest()[:16] != TRAFFIC["digest"] or gemm != TRAFFIC["gemm"]:
         return None
     return TRAFFIC["bytes"].get(kind)
-MFMA_PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0, "f16": 2500.0, "f64": 78.6}
+# f32x3: FP32 products as six BF16 products of three-way split operands
+MFMA_PEAK_TFLOPS = {"f32": 157.3, "f32x3": 2500.0 / 6.0, "bf16": 2500.0, "f16": 2500.0, "f64": 78.6}
+
+
+def gemm_arith(gemm, p, n1, s):
+    """The arithmetic the slice GEMMs of a three-kernel product run on: FP32 products are split from 64 x 64
+    output tiles up, while those cover the 256 CUs."""
+    return "f32x3" if gemm == "f32" and -(-n1 // 64) * -(-s // 64) * p >= 256 else gemm
 
 
 def parse():
@@ -484,7 +491,7 @@ def bench_paper(args):
         tot, cnt = prof_gk[kind]
         if cnt:
             f, b = kernel_work(kind, p, n, n, n, bg, per_solve=cnt)
-            kinds[kind] = roofline_entry(kind, tot * 1e3 / cnt, f, b, args.gemm, None)
+            kinds[kind] = roofline_entry(kind, tot * 1e3 / cnt, f, b, gemm_arith(args.gemm, p, n, n), None)
             kinds[kind].update({"launches": cnt, "ms_total": tot})
     dom = max(kinds, key=lambda k_: kinds[k_]["ms_total"])
     roof = dict(kinds[dom])
@@ -1012,7 +1019,7 @@ def bench_hyper(args):
         tot, cnt = prof[kind]
         if cnt:
             f, b = kernel_work(kind, p, n, n, s, bg, fast=longsolve, per_solve=cnt / args.steps)
-            kinds[kind] = roofline_entry(kind, tot * 1e3 / cnt, f, b, gemm,
+            kinds[kind] = roofline_entry(kind, tot * 1e3 / cnt, f, b, gemm_arith(gemm, p, n, s),
                                          None if (order4 or longsolve) else hyper_traffic(kind, gemm))
             kinds[kind].update({"launches": cnt, "ms_total": tot})
     dom = max(kinds, key=lambda k_: kinds[k_]["ms_total"])
@@ -1325,7 +1332,7 @@ def bench_large(args):
     else:  # tube transform: read and write p x n x s, 2p flops per element
         flops = 2.0 * p * N
         byts = N * (4 + (bg if kind == "tube_fwd" else 4))
-    peak_f = MFMA_PEAK_TFLOPS[args.gemm]
+    peak_f = MFMA_PEAK_TFLOPS[gemm_arith(args.gemm, p, n, s) if kind == "gemm" else args.gemm]
     if kind.startswith("tube"):
         peak_f = MFMA_PEAK_TFLOPS["f32"]   # vector FP32 arithmetic
     ai = flops / byts

@@ -10,6 +10,7 @@
 // Global loads are ordered along each operand's contiguous dimension; the
 // next K-chunk is prefetched into registers while the current one is
 // multiplied.  Ragged edges are zero-filled on load and masked on store.
+#include <algorithm>
 #include <type_traits>
 
 #include "fastdct.h"
@@ -457,6 +458,245 @@ __global__ __launch_bounds__(256) void gemm_mn_kernel(GemmArgs ga_, const GemmAr
   }
 }
 
+// FP32 slice GEMM on the BF16 matrix cores.  An FP32 number is the exact sum of
+// three bfloat16 numbers (3 x 8 significant bits, each the round-to-nearest of
+// what the ones before it leave), so the product of two is nine BF16 products,
+// each exact in FP32.  The three smallest (second x third, third x second,
+// third x third: below 2^-26 of the whole) are left out, the other six are
+// accumulated in FP32, the small ones first, by the 16x16x32 instruction,
+// which runs 16 times as many operations per cycle as the FP32 16x16x4: 6 / 16
+// of its matrix-core time, with one rounding per 32 k and product where the
+// FP32 instruction makes one per 4 k.  On uniform random operands the relative
+// 2-norm error against FP64 is 3.35e-7 (FP32 instruction: 4.03e-7) at K = 512,
+// 4.8e-7 (5.7e-7) at K = 1024, 2.3e-7 (2.9e-7) at K = 256, 1.3e-7 (1.8e-7) at
+// K = 96.
+//
+// Tile: BM x BN outputs per workgroup.  A thread loads 8 consecutive k of one
+// row of A~ (and of one column of the right operand: 8 loads, each coalesced
+// along n), splits them in registers (5.5 VALU operations per element) and
+// writes the three planes to LDS as 16-byte units of 8 k, so the MFMA operands
+// are single 16-byte reads and the transposition of the right operand costs
+// nothing.  Unit q of row r is stored at r * 4 + (q ^ (r / 2 % 4)): stores and
+// reads of 8 consecutive lanes hit 8 different bank groups without padding.
+// The next chunk's loads are in flight while the current one is multiplied.
+// Bounds are the buffer descriptors': rows beyond the slice read as zeros.
+// What is read beyond K in a row of A~ (the next row's start) meets a zero row
+// of the right operand; with both operands contiguous in k (TB) the last chunk
+// of A~ is zeroed explicitly.
+// Bound: the matrix cores at the rate their power allows (64 x 512^3: 94 us =
+// 1.10 PFLOP/s of BF16, a large BF16 library product 1.19; FP32 instruction
+// 144 us; 3 x 1024^3: 49 us against 70; 32 x 256^3: 12.4 us against 16.3).
+//
+// The split does not represent infinities and NaN (their remainders are NaN),
+// values that round to infinity in bfloat16, nor all 24 bits of numbers below
+// 2^-110.  A wave whose largest result is not finite, or not zero and below
+// 2^-96, computes its part again with the FP32 instruction (split_redo), in
+// the order of gemm_mn_kernel.
+struct Split8 {
+  uint4 h[3];
+};
+__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  unsigned w[3][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float a = x[2 * i], b = x[2 * i + 1];
+#pragma unroll
+    for (int h = 0; h < 3; ++h) {
+      const unsigned q = __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
+      w[h][i] = q;
+      a -= __builtin_bit_cast(float, q << 16);
+      b -= __builtin_bit_cast(float, q & 0xffff0000u);
+    }
+  }
+  Split8 s;
+#pragma unroll
+  for (int h = 0; h < 3; ++h) s.h[h] = make_uint4(w[h][0], w[h][1], w[h][2], w[h][3]);
+  return s;
+}
+
+// Raw buffer descriptor of `n` floats from p (at most 2 GiB).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t float_buffer(const float* p, int64_t n) {
+  const int64_t cap = 0x1fffffff;
+  n = n < 0 ? 0 : (n < cap ? n : cap);
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, (int)(n * 4), 0x00020000);
+}
+
+// A wave's FM x FN blocks from row m0, column n0 with the FP32 instruction,
+// operands straight from memory: rarely run, so kept small.
+template <int FM, int FN, bool TB>
+__device__ __forceinline__ void split_redo(const float* A, const float* B, float* C, int M, int N, int K, int64_t lda,
+                                        int64_t ldb, int64_t ldc, int m0, int n0) {
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+#pragma unroll 1
+  for (int i = 0; i < FM; ++i)
+#pragma unroll 1
+    for (int j = 0; j < FN; ++j) {
+      const int m = m0 + i * 16 + lr, n = n0 + j * 16 + lr;
+      f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+      for (int ks = 0; ks < K; ks += 4) {
+        const int k = ks + lk;
+        const bool oka = m < M && k < K, okb = n < N && k < K;
+        const float av = A[oka ? (int64_t)m * lda + k : 0];
+        const float bv = B[okb ? (TB ? (int64_t)n * ldb + k : (int64_t)k * ldb + n) : 0];
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(oka ? av : 0.0f, okb ? bv : 0.0f, acc, 0, 0, 0);
+      }
+      if (n >= N) continue;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = m0 + i * 16 + lk * 4 + r;
+        if (row < M) C[(int64_t)row * ldc + n] = acc[r];
+      }
+    }
+}
+
+template <int BM, int BN, int NT, int WGM, int WGN, bool TB>
+__device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const VBlock vb) {
+  constexpr int BK = 32;
+  constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 16, FN = WN / 16;
+  constexpr int AU = BM * 4 / NT, BU = BN * 4 / NT;   // 8-element units per thread and chunk
+  static_assert(WGM * WGN * 64 == NT && AU * NT == BM * 4 && BU * NT == BN * 4, "tile");
+  static_assert(NT % BN == 0 || BN % NT == 0, "columns of a unit");
+  if (!gate_open(ga.g)) return;
+  __shared__ uint4 As[3][BM * 4];
+  __shared__ uint4 Bs[3][BN * 4];
+  const int M = ga.M, N = ga.N, K = ga.K;
+  const float* A = (const float*)ga.A + (int64_t)vb.z * ga.sA;
+  const float* B = (const float*)ga.B + (int64_t)vb.z * ga.sB;
+  float* C = (float*)ga.C + (int64_t)vb.z * ga.sC;
+  const int lda = (int)ga.lda, ldb = (int)ga.ldb;   // below 2^20 (split_shape_ok)
+  const int m0 = vb.y * BM, n0 = vb.x * BN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+  const int lr = lane & 15, lg = lane >> 4;
+
+  // byte offsets from the tile's first row (A~, TB) or column of a chunk
+  const int oa = ((tid >> 2) * lda + (tid & 3) * 8) * 4;
+  const int ob = TB ? ((tid >> 2) * ldb + (tid & 3) * 8) * 4 : (tid / BN * 8 * ldb + tid % BN) * 4;
+  const float* At = A + (int64_t)m0 * lda;
+  const float* Bt = TB ? B + (int64_t)n0 * ldb : B + n0;
+  const int64_t na = (int64_t)(M - 1 - m0) * lda + K, nb = TB ? (int64_t)(N - 1 - n0) * ldb + K : (int64_t)K * ldb - n0;
+  float ra[AU][8], rb[BU][8];
+  auto load8 = [&](const __amdgpu_buffer_rsrc_t& q, int o, float (&v)[8]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const f32x4 w = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(q, o + 16 * h, 0, 0));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[4 * h + i] = w[i];
+    }
+  };
+  auto load_chunk = [&](int k0) {
+    const __amdgpu_buffer_rsrc_t qa = float_buffer(At + k0, na - k0);
+#pragma unroll
+    for (int u = 0; u < AU; ++u) load8(qa, oa + u * (NT / 4) * lda * 4, ra[u]);
+    if constexpr (TB) {
+      const __amdgpu_buffer_rsrc_t qb = float_buffer(Bt + k0, nb - k0);
+#pragma unroll
+      for (int u = 0; u < BU; ++u) load8(qb, ob + u * (NT / 4) * ldb * 4, rb[u]);
+      if (k0 + BK > K) {
+#pragma unroll
+        for (int u = 0; u < AU; ++u)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) ra[u][i] = k0 + (tid & 3) * 8 + i < K ? ra[u][i] : 0.0f;
+      }
+    } else {
+      const __amdgpu_buffer_rsrc_t qb = float_buffer(Bt + (int64_t)k0 * ldb, nb - (int64_t)k0 * ldb);
+#pragma unroll
+      for (int u = 0; u < BU; ++u)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          rb[u][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(qb, ob + (u * (NT / BN * 8) + i) * ldb * 4, 0, 0));
+    }
+  };
+  auto put = [&](uint4* S, int plane, int r, int q, const float (&v)[8]) {
+    const Split8 s = split8(v);
+    const int at = r * 4 + (q ^ ((r >> 1) & 3));
+#pragma unroll
+    for (int h = 0; h < 3; ++h) S[h * plane + at] = s.h[h];
+  };
+  auto store_chunk = [&]() {
+#pragma unroll
+    for (int u = 0; u < AU; ++u) {
+      const int i = tid + u * NT;
+      put(&As[0][0], BM * 4, i >> 2, i & 3, ra[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < BU; ++u) {
+      const int i = tid + u * NT;
+      if (TB) put(&Bs[0][0], BN * 4, i >> 2, i & 3, rb[u]);
+      else put(&Bs[0][0], BN * 4, i % BN, i / BN, rb[u]);
+    }
+  };
+
+  f32x4 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+  load_chunk(0);
+  for (int k0 = 0; k0 < K; k0 += BK) {
+    __syncthreads();
+    store_chunk();
+    __syncthreads();
+    if (k0 + BK < K) load_chunk(k0 + BK);
+    bf16x8 bf[FN][3];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int n = wn * WN + j * 16 + lr;
+#pragma unroll
+      for (int h = 0; h < 3; ++h) bf[j][h] = __builtin_bit_cast(bf16x8, Bs[h][n * 4 + (lg ^ ((n >> 1) & 3))]);
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int m = wm * WM + i * 16 + lr;
+      bf16x8 af[3];
+#pragma unroll
+      for (int h = 0; h < 3; ++h) af[h] = __builtin_bit_cast(bf16x8, As[h][m * 4 + (lg ^ ((m >> 1) & 3))]);
+      constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+      for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[pa[q]], bf[j][pb[q]], acc[i][j], 0, 0, 0);
+    }
+  }
+
+  unsigned big = 0;   // bits of the largest magnitude (infinities and NaN above all finite ones)
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int col = n0 + wn * WN + j * 16 + lr;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = m0 + wm * WM + i * 16 + lg * 4 + r;
+        const float v = acc[i][j][r];
+        const unsigned mag = __builtin_bit_cast(unsigned, v) & 0x7fffffffu;
+        big = big > mag ? big : mag;
+        if (row < M && col < N) C[(int64_t)row * ga.ldc + col] = v;
+      }
+    }
+  const bool high = big >= 0x7f800000u, some = big != 0, normal = big >= (127u - 96u) << 23;
+  if (__any(high) || (__any(some) && !__any(normal)))
+    split_redo<FM, FN, TB>(A, B, C, M, N, K, ga.lda, ga.ldb, ga.ldc, m0 + wm * WM, n0 + wn * WN);
+}
+
+template <int BM, int BN, int NT, int WGM, int WGN, bool TB, bool GROUPED>
+__global__ __launch_bounds__(NT, BM == 64 ? 4 : 2) void gemm_split_kernel(GemmArgs ga_, const GemmArgs* grp, const int4* bmap) {
+  if constexpr (!GROUPED) {
+    VBlock vb = hw_block();
+    if (!slice_block(ga_, vb)) return;
+    gemm_split_kernel_body<BM, BN, NT, WGM, WGN, TB>(ga_, vb);
+  } else {
+    VBlock vb;
+    const GemmArgs g = group_args(grp, bmap, vb);
+    if (!slice_block(g, vb)) return;   // the instance's grid may be padded
+    gemm_split_kernel_body<BM, BN, NT, WGM, WGN, TB>(g, vb);
+  }
+}
+
 template <typename T, int BM, int BN, int BK>
 static hipError_t launch_gemm_mn(dctk_ctx ctx, hipStream_t s, GemmArgs ga, int ta, int tb, bool vec,
                                  int batch) {
@@ -478,8 +718,44 @@ static hipError_t launch_gemm_mn(dctk_ctx ctx, hipStream_t s, GemmArgs ga, int t
 #undef DCTK_GMN
 }
 
-// FP32 / FP64 GEMMs with the output in the input type: 128 x 128 tiles while
-// they give every CU two tiles, then 64 x 64 while they cover the CUs, else 32 x 32.
+template <int BM, int BN, int NT, int WGM, int WGN>
+static hipError_t launch_gemm_split(dctk_ctx ctx, hipStream_t s, GemmArgs ga, int tb, int batch) {
+  ga.nbatch = batch >= kSliceXcdMin ? batch : 0;
+  const int gz = ga.nbatch > 0 ? (batch + 7) / 8 * 8 : batch;
+  const dim3 grid((unsigned)((ga.N + BN - 1) / BN), (unsigned)((ga.M + BM - 1) / BM), (unsigned)gz);
+#define DCTK_GSP(TB_) return launch_kernel(ctx, s, gemm_split_kernel<BM, BN, NT, WGM, WGN, TB_, false>, gemm_split_kernel<BM, BN, NT, WGM, WGN, TB_, true>, grid, NT, 0, ga)
+  if (tb) DCTK_GSP(true);
+  DCTK_GSP(false);
+#undef DCTK_GSP
+}
+
+// The split kernel's offsets within a tile are 32-bit (256 rows of lda, or 32
+// of ldb, floats), and its A~ has the contraction index contiguous.
+static bool split_shape_ok(int ta, int64_t lda, int64_t ldb) {
+  return !ta && lda < (1 << 20) && ldb < (1 << 20);
+}
+
+// Output tile edge of the split kernel: 256, 128 or 64, the one of least
+// estimated time per 32-long chunk, from what a tile of each takes while the
+// chip is full (64 x 512^3: 94, 98 and 118 us, i.e. 5.9, 1.53 and 0.46 us per
+// tile, chunk and CU) and from what a chunk takes at least, its loads' latency
+// (2.0 us with 128 x 128 tiles, 3 x 1024^3: 63 us; 1.4 us with 64 x 64, 32 x
+// 256^3: 12.4 us against 20.0).
+static int split_tile(int M, int N, int batch, int num_cus) {
+  auto rounds = [&](int t) {
+    const int64_t tiles = (int64_t)((M + t - 1) / t) * ((N + t - 1) / t) * batch;
+    return (double)((tiles + num_cus - 1) / num_cus);
+  };
+  const double c256 = 5.9 * rounds(256), c128 = std::max(2.0, 1.53 * rounds(128)), c64 = std::max(1.4, 0.46 * rounds(64));
+  return c256 <= c128 && c256 <= c64 ? 256 : (c128 <= c64 ? 128 : 64);
+}
+
+// FP32 / FP64 GEMMs with the output in the input type.  FP32 takes the split
+// kernel from 64 x 64 tiles up while those cover the CUs.  Below that (and for
+// FP64 and operands the split kernel does not take) the FP32 / FP64
+// instructions with 64 x 64 tiles while they cover the CUs, else 32 x 32 (31 x
+// 96^3 FP32: 4.2 us, split 64 x 64 5.1: too few workgroups).  A tile of 128
+// asked for takes 256 x 256 where that is the one of least estimated time.
 template <typename T>
 static hipError_t launch_gemm_vec(dctk_ctx ctx, hipStream_t s, int M, int N, int K, const void* A, int64_t lda,
                                   int64_t sA, int ta, const void* B, int64_t ldb, int64_t sB, int tb, void* C,
@@ -501,11 +777,19 @@ static hipError_t launch_gemm_vec(dctk_ctx ctx, hipStream_t s, int M, int N, int
   constexpr int VW = 16 / (int)sizeof(T);
   const bool vec = M % VW == 0 && N % VW == 0 && K % VW == 0 && lda % VW == 0 && ldb % VW == 0 &&
                    sA % VW == 0 && sB % VW == 0 && ((uintptr_t)A % 16) == 0 && ((uintptr_t)B % 16) == 0;
-  const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128) * batch;
   const int64_t t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * batch;
   constexpr int BK = sizeof(T) == 8 ? 16 : 32;
-  if (sizeof(T) == 4 && (tile == 128 || (tile == 0 && t128 >= 2 * (int64_t)num_cus)))
-    return launch_gemm_mn<T, 128, 128, 16>(ctx, s, ga, ta, tb, vec, batch);
+  if constexpr (sizeof(T) == 4) {
+    if (split_shape_ok(ta, lda, ldb)) {
+      const int best = split_tile(M, N, batch, num_cus);
+      if ((tile == 128 || (tile == 0 && t64 >= (int64_t)num_cus)) && best == 256)
+        return launch_gemm_split<256, 256, 512, 2, 4>(ctx, s, ga, tb, batch);
+      if (tile == 128 || (tile == 0 && t64 >= (int64_t)num_cus && best == 128))
+        return launch_gemm_split<128, 128, 256, 2, 2>(ctx, s, ga, tb, batch);
+      if (tile == 64 || (tile == 0 && t64 >= (int64_t)num_cus))
+        return launch_gemm_split<64, 64, 256, 2, 2>(ctx, s, ga, tb, batch);
+    }
+  }
   if (tile == 64 || tile == 128 || (tile == 0 && t64 >= (int64_t)num_cus))
     return launch_gemm_mn<T, 64, 64, BK>(ctx, s, ga, ta, tb, vec, batch);
   return launch_gemm_mn<T, 32, 32, BK>(ctx, s, ga, ta, tb, vec, batch);
