@@ -646,12 +646,15 @@ int dctk_krylov_create(dctk_ctx ctx, dctk_op op, int kind, int k_max, int ortho,
   if (e == hipSuccess) e = hipMalloc((void**)&ws->partA, sizeof(double) * kNormParts);
   if (e == hipSuccess) e = hipMalloc((void**)&ws->partB, sizeof(double) * kNormParts);
   if (e == hipSuccess) e = hipMalloc((void**)&ws->partM, sizeof(double) * kRedBlocks * kRedVals);
+  const size_t gbytes = sizeof(double) * kMaxK * kMaxK;
+  if (e == hipSuccess && kind == DCTK_KRYLOV_ARNOLDI) e = hipMalloc((void**)&ws->gram, gbytes);
+  if (e == hipSuccess && kind == DCTK_KRYLOV_ARNOLDI) e = hipMemset(ws->gram, 0, gbytes);
   if (e == hipSuccess) e = hipMalloc((void**)&ws->st, sizeof(KState));
   if (e == hipSuccess) e = hipMemset(ws->st, 0, sizeof(KState));
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     int st = hip_fail(ctx, e);
-    void* ptrs[] = {ws->U, ws->V, ws->X, ws->W, ws->T, ws->R, ws->partA, ws->partB, ws->partM, ws->st};
+    void* ptrs[] = {ws->U, ws->V, ws->X, ws->W, ws->T, ws->R, ws->partA, ws->partB, ws->partM, ws->gram, ws->st};
     for (void* q : ptrs)
       if (q) (void)hipFree(q);
     delete ws;
@@ -665,7 +668,7 @@ int dctk_krylov_destroy(dctk_krylov ws) {
   if (!ws) return DCTK_EINVAL;
   (void)hipSetDevice(ws->op->ctx->device);
   (void)hipStreamSynchronize(ws->op->ctx->stream);
-  void* ptrs[] = {ws->U, ws->V, ws->X, ws->W, ws->T, ws->R, ws->partA, ws->partB, ws->partM, ws->st};
+  void* ptrs[] = {ws->U, ws->V, ws->X, ws->W, ws->T, ws->R, ws->partA, ws->partB, ws->partM, ws->gram, ws->st};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   delete ws;
@@ -924,18 +927,9 @@ static hipError_t arnoldi_step_impl(dctk_ctx ctx, dctk_krylov ws, int j) {
   double* Hcol = &st->H[j - 1];  // H[i][j-1] at Hcol[i * kMaxK]
   int np = 0;
   if (ws->ortho == DCTK_ORTHO_MGS) {
-    // h_{i,j} = <V_i, W>; W -= h_{i,j} V_i, as: record and subtract the previous term, then dot with V_i
-    const double* pin = nullptr;
-    int npin = 0;
-    for (int i = 0; i <= j; ++i) {
-      double* pout = (i == j) ? ws->partA : ((i & 1) ? ws->partM : ws->partB);
-      const void* vprev = i > 0 ? slot(ws->U, ws, i - 1) : nullptr;
-      const void* vi = i < j ? slot(ws->U, ws, i) : nullptr;
-      double* hdst = i > 0 ? &Hcol[(i - 1) * kMaxK] : nullptr;
-      if ((e = launch_mgs(ctx, vdt, n, W, vprev, vi, pin, npin, hdst, pout, &np, st, j)) != hipSuccess) return e;
-      pin = pout;
-      npin = np;
-    }
+    if ((e = launch_arn_mgs(ctx, vdt, n, W, ws->U, ws->nvec, j, ws->gram, st->coef, Hcol, ws->partM, ws->partA, &np,
+                            st)) != hipSuccess)
+      return e;
   } else {
     const Gate g{st, j - 1, 1};
     if ((e = cgs2(ctx, ws, ws->U, j, W, n, g, Hcol)) != hipSuccess) return e;

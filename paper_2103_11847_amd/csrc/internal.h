@@ -630,6 +630,7 @@ struct dctk_krylov_s {
   double* partA;           // kNormParts partials (norms feeding the next product)
   double* partB;           // kNormParts partials
   double* partM;           // kRedBlocks * kRedVals partials of multi-dots
+  double* gram;            // Arnoldi: kMaxK x kMaxK inner products of the basis vectors so far
   dctk::KState* st;        // device state
 };
 
@@ -802,11 +803,12 @@ hipError_t launch_combine(dctk_ctx ctx, int dtype, int64_t n, void* out, const v
 // GMRES cycle start: beta = sqrt(sum part) -> st->beta0 (halt on 0); out = in / beta
 hipError_t launch_arn_start(dctk_ctx ctx, int dtype, int64_t n, void* out, const void* in, const double* part,
                             int npart, KState* st);
-// Arnoldi MGS pass i of step j: when part_in, h = sum part_in is recorded at hdst and
-// w -= h * vprev; then partials of <vi, w> (vi null: |w|^2) into part_out
-hipError_t launch_mgs(dctk_ctx ctx, int dtype, int64_t n, void* w, const void* vprev, const void* vi,
-                      const double* part_in, int npart_in, double* hdst, double* part_out, int* nblocks,
-                      KState* st, int j);
+// Arnoldi step nb: the modified Gram-Schmidt coefficients of w against the nb basis
+// vectors into coef and hcol (row stride kMaxK), w -= sum of them, partials of ||w||^2
+// into part_out; part: scratch for 2 nb x 512 partials, gram: the basis' Gram rows so far
+hipError_t launch_arn_mgs(dctk_ctx ctx, int dtype, int64_t n, void* w, const void* basis, int64_t stride, int nb,
+                          double* gram, double* coef, double* hcol, double* part, double* part_out, int* nblocks,
+                          KState* st);
 // Arnoldi: record h_{j+1,j} = sqrt(sum part) with the breakdown test (one block)
 hipError_t launch_arn_finish(dctk_ctx ctx, const double* part, int npart, KState* st, int j);
 // GMRES: ||C - M(X)|| = sqrt(sum part) with the convergence test (one block)
