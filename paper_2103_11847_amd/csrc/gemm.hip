@@ -888,15 +888,20 @@ bool fused_eligible(dctk_op op) {
 }
 
 // Without a tuned choice: the fused product while the problem is small enough to
-// be latency-bound (fewer 32 x 32 output tiles than CUs) and its transforms stay
-// cheap next to the slice GEMMs (p <= 4, or small slices); else transform, GEMM,
-// transform.
+// be latency-bound (fewer 32 x 32 output tiles than CUs) and its in-register
+// transforms are cheap (p <= 4; FP64, whose transforms cost the unfused path
+// more, also p <= 8 with slices up to 112^3); else transform, GEMM, transform.
+// Time per product, fused / three kernels (us): FP32 p = 3, n = 256: 6.7 /
+// 12.9, n = 230: 12.9 / 14.6; p = 5, n = 64: 13.9 / 12.5; p = 8, n = 32: 18.5 /
+// 13.7, n = 128: 29.0 / 15.7, n = 192: 40.5 / 18.1; BF16 p = 8, n = 128: 31.3 /
+// 16.9; FP64 p = 8, n = 96: 17.3 / 19.0, n = 115: 29.2 / 23.9, p = 5, n = 153:
+// 23.7 / 22.0.
 bool use_fused(dctk_op op, int adjoint) {
   const int path = op->tune[adjoint ? 1 : 0][0];
   if (path >= 0) return path == 1;
   const int64_t M = adjoint ? op->n2 : op->n1, K = adjoint ? op->n1 : op->n2, N = op->s;
   const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32);
-  return t32 < g_num_cus && (op->p <= 4 || M * N * K <= (int64_t)192 * 192 * 192);
+  return t32 < g_num_cus && (op->p <= 4 || (op->gemm_dtype == DCTK_F64 && M * N * K <= (int64_t)112 * 112 * 112));
 }
 
 // The GEMM's gate under a product's control block: it runs unless the process
@@ -947,6 +952,10 @@ static hipError_t slice_gemms(dctk_op op, hipStream_t s, int adjoint, const Gate
 }
 
 bool pair_eligible(dctk_op op) {
+  // short tubes only with FP32 slice products: pairing rounds the next product's
+  // input from the unnormalised vector, whose scale FP16 does not bear as well
+  // as the normalised one's, and 16-bit short-tube solves keep their roundings
+  if (op->p < 16 && op->gemm_dtype != DCTK_F32) return false;
   return !op->fast && tube_pair_ok(op->p, op->vec_dtype) &&
          !(fused_eligible(op) && (use_fused(op, 0) || use_fused(op, 1)));
 }

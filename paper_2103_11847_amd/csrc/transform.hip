@@ -781,6 +781,131 @@ __device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const 
   }
 }
 
+// The same pair of transforms for short tubes (p <= 8): a thread holds the p
+// entries of four neighbouring tubes in registers, so y = a (G1 c) + b src and
+// x = G1^T y follow each other without LDS or barriers, with every load of c
+// and src in flight together (16 rows of 16 bytes per thread at p = 8).  Bound
+// by memory (16 B/element at 4 p flops); inside a Golub-Kahan step it replaces
+// the inverse and the forward transform's own launches and the re-read of y.
+template <typename TX, int KB, bool VEC>
+__device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const VBlock vb) {
+  __shared__ float sG[KB * KB];
+  __shared__ double sh[kShCtl];
+  const int p = pa.p;
+  const int64_t count = pa.count;
+  const bool has_src = pa.src != nullptr;
+  const float* in = pa.c;
+  const float* src = has_src ? pa.src : pa.c;   // without src its loads read c again and are not used
+  const int64_t stride = (int64_t)pa.gx * kThreads * 4;
+  float cv[KB][4], sv[KB][4];
+  auto load = [&](int64_t e0) {
+#pragma unroll
+    for (int t = 0; t < KB; ++t) {
+      const int64_t row = (int64_t)(t < p ? t : 0) * count;
+      if constexpr (VEC) {
+        const int64_t o = row + (e0 < count ? e0 : 0);
+        Vec4Load<float>::load(in + o, cv[t]);
+        Vec4Load<float>::load(src + o, sv[t]);
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int64_t o = row + (e0 + v < count ? e0 + v : 0);
+          cv[t][v] = in[o];
+          sv[t][v] = src[o];
+        }
+      }
+    }
+  };
+  int64_t e0 = ((int64_t)vb.x * kThreads + threadIdx.x) * 4;
+  // the first tubes, the matrix and the control block's values in flight together
+  const CtlLoad cl = ctl_load(pa.ctl);
+  const int gi = (int)threadIdx.x;
+  const float g = pa.G1[gi < p * p ? gi : 0];
+  load(e0);
+  double a_d, b_d, s_d;
+  if (!ctl_eval(pa.ctl, cl, a_d, b_d, s_d, sh, vb)) return;
+  const float a = (float)(a_d * s_d), b = has_src ? (float)b_d : 0.0f;
+  const bool use_src = b != 0.0f;   // b = 0: src never enters
+  if (gi < p * p) sG[gi / p * KB + gi % p] = g;
+  __syncthreads();
+  double sq = 0.0;
+  for (; e0 < count; e0 += stride) {
+    float y[KB][4];
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+      float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (k < p) {
+#pragma unroll
+        for (int t = 0; t < KB; ++t)
+          if (t < p) {
+            const float w = sG[k * KB + t];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[v] += w * cv[t][v];
+          }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float r = a * acc[v];
+        if (use_src) r += b * sv[k][v];
+        y[k][v] = r;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+      if (k >= p) break;
+      float* op = pa.y + (int64_t)k * count + e0;
+      if constexpr (VEC) {
+        RowStore<float>::st(op, y[k]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) sq += (double)y[k][v] * (double)y[k][v];
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (e0 + v < count) {
+            op[v] = y[k][v];
+            sq += (double)y[k][v] * (double)y[k][v];
+          }
+      }
+    }
+    if (e0 + stride < count) load(e0 + stride);
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+      if (k >= p) break;
+      float x[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int t = 0; t < KB; ++t)
+        if (t < p) {
+          const float w = sG[t * KB + k];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) x[v] += w * y[t][v];
+        }
+      TX* xp = (TX*)pa.x + (int64_t)k * count + e0;
+      if constexpr (VEC) {
+        RowStore<TX>::st(xp, x);
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (e0 + v < count) xp[v] = cvt<TX, float>(x[v]);
+      }
+    }
+  }
+  if (pa.ctl.part_out != nullptr) {
+    const double tot = block_sum_all(sq, sh);
+    if (threadIdx.x == 0) pa.ctl.part_out[vb.x] = tot;
+  }
+}
+
+template <typename TX, int KB, bool VEC, bool GROUPED>
+__global__ __launch_bounds__(kThreads) void tube_pair_small_kernel(PairArgs pa_, const PairArgs* grp, const int4* bmap) {
+  if constexpr (!GROUPED) {
+    tube_pair_small_body<TX, KB, VEC>(pa_, hw_block());
+  } else {
+    VBlock vb;
+    const PairArgs g = group_args(grp, bmap, vb);
+    tube_pair_small_body<TX, KB, VEC>(g, vb);
+  }
+}
+
 template <typename TX, int PM, bool VEC, bool GROUPED>
 __global__ __launch_bounds__(256) void tube_pair_kernel(PairArgs pa_, const PairArgs* grp, const int4* bmap) {
   if constexpr (!GROUPED) {
@@ -792,14 +917,16 @@ __global__ __launch_bounds__(256) void tube_pair_kernel(PairArgs pa_, const Pair
   }
 }
 
-bool tube_pair_ok(int64_t p, int vec_dtype) { return vec_dtype == DCTK_F32 && p >= 16 && p <= kMaxTube; }
+bool tube_pair_ok(int64_t p, int vec_dtype) { return vec_dtype == DCTK_F32 && (p <= 8 || p >= 16) && p <= kMaxTube; }
 
 hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p, int64_t count, const float* c,
                             const float* src, float* y, void* x, const float* G1, const Ctl& ctl,
                             int* nblocks_out) {
   if (!tube_pair_ok(p, DCTK_F32)) return hipErrorInvalidValue;
-  // four workgroups per CU (36 KB of LDS each), each walking several tiles
-  int64_t blocks = (count + 63) / 64;
+  // four workgroups per CU (36 KB of LDS each), each walking several tiles of
+  // 64 positions; short tubes: 1024 positions per workgroup and turn
+  const bool small = p <= 8;
+  int64_t blocks = small ? (count + 4 * kThreads - 1) / (4 * kThreads) : (count + 63) / 64;
   const int64_t cap = 4 * (int64_t)num_cus();
   if (blocks > cap) blocks = cap;
   if (nblocks_out) *nblocks_out = (int)blocks;
@@ -822,8 +949,15 @@ hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p,
     if (vec) return launch_kernel(ctx, s, tube_pair_kernel<TX, PM_, true, false>, tube_pair_kernel<TX, PM_, true, true>, grid, 256, 0, pa); \
     return launch_kernel(ctx, s, tube_pair_kernel<TX, PM_, false, false>, tube_pair_kernel<TX, PM_, false, true>, grid, 256, 0, pa); \
   } while (0)
+#define DCTK_PAIR_S(TX, KB_)                                                                                     \
+  do {                                                                                                         \
+    if (vec) return launch_kernel(ctx, s, tube_pair_small_kernel<TX, KB_, true, false>, tube_pair_small_kernel<TX, KB_, true, true>, grid, kThreads, 0, pa); \
+    return launch_kernel(ctx, s, tube_pair_small_kernel<TX, KB_, false, false>, tube_pair_small_kernel<TX, KB_, false, true>, grid, kThreads, 0, pa); \
+  } while (0)
 #define DCTK_PAIR_P(TX)            \
   do {                             \
+    if (p <= 4) DCTK_PAIR_S(TX, 4);   \
+    if (p <= 8) DCTK_PAIR_S(TX, 8);   \
     if (p <= 16) DCTK_PAIR_V(TX, 16); \
     if (p <= 32) DCTK_PAIR_V(TX, 32); \
     if (p <= 48) DCTK_PAIR_V(TX, 48); \
@@ -836,6 +970,7 @@ hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p,
     default: return hipErrorInvalidValue;
   }
 #undef DCTK_PAIR_P
+#undef DCTK_PAIR_S
 #undef DCTK_PAIR_V
 }
 
