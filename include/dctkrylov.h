@@ -436,8 +436,13 @@ int dctk_lsqr_learned_solve(dctk_ctx ctx, dctk_krylov ws, dctk_mlp mlp, const vo
  * the launches of one kernel at the same point of the schedule are merged,
  * across instances, into one launch whose workgroups each look up their
  * instance; the resulting schedule (one launch per kernel variant per
- * schedule point) is captured once into a HIP graph.  Every instance computes
- * exactly what its own dctk_lsqr_tik_solve would.
+ * schedule point) is captured once into HIP graphs, one for each of up to three
+ * classes of instances whose products launch different kernels; the graphs run
+ * beside each other, the first on ctx's stream, the others on two streams that
+ * the plans of a device share, between what ctx's stream held before the run
+ * and what it is given after it.  (A stream under capture takes the launches
+ * themselves, in order.)  Every instance computes exactly what its own
+ * dctk_lsqr_tik_solve would.
  *
  * dctk_batch_create: count in [1, DCTK_BATCH_MAX]; ws[i] DCTK_KRYLOV_GKB
  *   workspaces of distinct operators on ctx's device (the products of a batch
