@@ -106,8 +106,8 @@ int dctk_version(void);
  * fused forward product M(X), 4 one fused adjoint product M*(Y), 5 an
  * inverse transform with its epilogue paired with the next product's forward
  * transform (the Golub-Kahan steps of a Tikhonov solve with three-kernel
- * products and FP32 vectors, 16 <= p <= 64, or p <= 8 with FP32 slice
- * products).
+ * products and FP32 vectors, p <= 64 (below 16 only with FP32 slice
+ * products)).
  * Error: DCTK_ESTATE if not profiling. */
 #define DCTK_PROF_KINDS 6
 int dctk_profile_begin(dctk_ctx ctx);

@@ -740,7 +740,7 @@ hipError_t launch_tube(dctk_ctx ctx, hipStream_t st, int in_dtype, int out_dtype
 
 // Inverse transform of one product with its epilogue, y = a (G1 c) + b src (a scaled
 // by the control block's input scale; partials of y^2 in ctl.part_out), paired with
-// the next product's forward transform x = G1^T y in x_dtype (FP32 vectors, p <= 8 or 16 <= p <= 64).
+// the next product's forward transform x = G1^T y in x_dtype (FP32 vectors, p <= 64).
 // G1 is L^{-1} after a forward product (then G1^T = L^{-T}), L^T after an adjoint (G1^T = L).
 bool tube_pair_ok(int64_t p, int vec_dtype);
 hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p, int64_t count, const float* c,
@@ -767,7 +767,8 @@ hipError_t apply_op(dctk_op op, hipStream_t s, int adjoint, const void* X, void*
                     void* xnorm, const Ctl& ctl, int* nblocks_out);
 
 // Golub-Kahan steps with paired transforms (three-kernel products, FP32 vectors,
-// 16 <= p <= 64, or p <= 8 with FP32 slice products): pair_eligible says whether op takes them; pair_first enqueues
+// p <= 64, below 16 only with FP32 slice products): pair_eligible says whether op
+// takes them; pair_first enqueues
 // a product's forward transform (input X, scale from ctl) and its slice GEMMs;
 // pair_gemm the slice GEMMs of a product whose transformed input is already in
 // place; pair_transforms the product's inverse transform with its epilogue

@@ -4,9 +4,9 @@
 // position e of a frontal slice, out[k][e] = sum_t G[k][t] in[t][e].  With the
 // slice-major layout the p inputs of a tube are p slices apart, so a thread
 // streams VEC consecutive positions of every slice (coalesced 16-byte loads
-// along the slice) and keeps KB outputs in registers per pass; G sits in LDS.
-// The work is HBM-bound for the p of colour images and video (2p flops per
-// 2 elements moved).
+// along the slice) and keeps its tubes in registers; G sits in LDS.  Tubes
+// longer than 8 run on the matrix cores.  The work is HBM-bound for the p of
+// colour images and video (2p flops per 2 elements moved).
 #include <cmath>
 #include <vector>
 
@@ -140,151 +140,87 @@ __device__ __forceinline__ void tube_kernel_body(const TubeArgs& ta, const VBloc
   __syncthreads();
   double sq = 0.0;
   const int64_t stride = (int64_t)ta.gx * blockDim.x * 4;
-  if (p <= KB) {
-    // all p tubes of a 4-position group at once: every input (and src) load
-    // of the group is issued before the first use, from clamped addresses
-    const bool use_src = EPI && src != nullptr && b != (TC)0;
-    const TOUT* srcl = use_src ? src : out;
-    for (int64_t e0 = ((int64_t)vb.x * blockDim.x + threadIdx.x) * 4; e0 < count; e0 += stride) {
-      const int nv = (count - e0) < 4 ? (int)(count - e0) : 4;
-      TIN xv[KB][4];
-      if (VEC && nv == 4) {
+  // all p tubes of a 4-position group at once: every input (and src) load
+  // of the group is issued before the first use, from clamped addresses
+  const bool use_src = EPI && src != nullptr && b != (TC)0;
+  const TOUT* srcl = use_src ? src : out;
+  for (int64_t e0 = ((int64_t)vb.x * blockDim.x + threadIdx.x) * 4; e0 < count; e0 += stride) {
+    const int nv = (count - e0) < 4 ? (int)(count - e0) : 4;
+    TIN xv[KB][4];
+    if (VEC && nv == 4) {
 #pragma unroll
-        for (int t = 0; t < KB; ++t) {
-          Vec4Load<TIN>::load(in + (int64_t)(t < p ? t : 0) * count + e0, xv[t]);
-          if (t >= p) {
+      for (int t = 0; t < KB; ++t) {
+        Vec4Load<TIN>::load(in + (int64_t)(t < p ? t : 0) * count + e0, xv[t]);
+        if (t >= p) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) xv[t][v] = (TIN)0;
-          }
+          for (int v = 0; v < 4; ++v) xv[t][v] = (TIN)0;
         }
-      } else {
-#pragma unroll
-        for (int t = 0; t < KB; ++t)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const bool ok = t < p && v < nv;
-            const TIN x = in[ok ? (int64_t)t * count + e0 + v : 0];
-            xv[t][v] = ok ? x : (TIN)0;
-          }
       }
-      TC sv[KB][4];
+    } else {
+#pragma unroll
+      for (int t = 0; t < KB; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const bool ok = t < p && v < nv;
+          const TIN x = in[ok ? (int64_t)t * count + e0 + v : 0];
+          xv[t][v] = ok ? x : (TIN)0;
+        }
+    }
+    TC sv[KB][4];
+#pragma unroll
+    for (int k = 0; k < KB; ++k)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sv[k][v] = (TC)0;
+    if (use_src) {
 #pragma unroll
       for (int k = 0; k < KB; ++k)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) sv[k][v] = (TC)0;
-      if (use_src) {
-#pragma unroll
-        for (int k = 0; k < KB; ++k)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const bool ok = k < p && v < nv;
-            const TOUT x = srcl[ok ? (int64_t)k * count + e0 + v : 0];
-            sv[k][v] = ok ? (TC)x : (TC)0;
-          }
-      }
-      if (SCALE) {
-#pragma unroll
-        for (int t = 0; t < KB; ++t)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) xv[t][v] = (TIN)(sc * (TC)xv[t][v]);
-        if (xnorm != nullptr) {
-#pragma unroll
-          for (int t = 0; t < KB; ++t) {
-            if (t < p) {
-              TIN* xp = xnorm + (int64_t)t * count + e0;
-              if (VEC && nv == 4) Vec4Store<TIN>::store(xp, xv[t]);
-              else for (int v = 0; v < nv; ++v) xp[v] = xv[t][v];
-            }
-          }
+        for (int v = 0; v < 4; ++v) {
+          const bool ok = k < p && v < nv;
+          const TOUT x = srcl[ok ? (int64_t)k * count + e0 + v : 0];
+          sv[k][v] = ok ? (TC)x : (TC)0;
         }
-      }
+    }
+    if (SCALE) {
 #pragma unroll
-      for (int k = 0; k < KB; ++k) {
-        if (k >= p) break;
-        TC acc[4] = {(TC)0, (TC)0, (TC)0, (TC)0};
+      for (int t = 0; t < KB; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) xv[t][v] = (TIN)(sc * (TC)xv[t][v]);
+      if (xnorm != nullptr) {
 #pragma unroll
         for (int t = 0; t < KB; ++t) {
-          const TC gk = t < p ? sG[k * p + t] : (TC)0;
-#pragma unroll
-          for (int v = 0; v < 4; ++v) acc[v] += gk * (TC)xv[t][v];
-        }
-        TOUT ov[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          TC r = a * acc[v];
-          if (EPI) r += b * sv[k][v];
-          ov[v] = cvt<TOUT, TC>(r);
-          if (EPI && v < nv) {
-            const double rv = (double)r;
-            sq += rv * rv;
-          }
-        }
-        TOUT* op = out + (int64_t)k * count + e0;
-        if (VEC && nv == 4) Vec4Store<TOUT>::store(op, ov);
-        else for (int v = 0; v < nv; ++v) op[v] = ov[v];
-      }
-    }
-    if (EPI && ctl.part_out != nullptr) {
-      const double tot = block_sum_all(sq, sh);
-      if (threadIdx.x == 0) ctl.part_out[vb.x] = tot;
-    }
-    return;
-  }
-  for (int64_t e0 = ((int64_t)vb.x * blockDim.x + threadIdx.x) * 4; e0 < count; e0 += stride) {
-    const int nv = (count - e0) < 4 ? (int)(count - e0) : 4;
-    for (int k0 = 0; k0 < p; k0 += KB) {
-      TC acc[KB][4];
-#pragma unroll
-      for (int kk = 0; kk < KB; ++kk)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[kk][v] = (TC)0;
-      for (int t = 0; t < p; ++t) {
-        TIN xv[4];
-        const TIN* ip = in + (int64_t)t * count + e0;
-        if (VEC && nv == 4) {
-          Vec4Load<TIN>::load(ip, xv);
-        } else {
-#pragma unroll
-          for (int v = 0; v < 4; ++v) xv[v] = v < nv ? ip[v] : (TIN)0;
-        }
-        if (SCALE) {
-#pragma unroll
-          for (int v = 0; v < 4; ++v) xv[v] = (TIN)(sc * (TC)xv[v]);
-          if (xnorm != nullptr && k0 == 0) {
+          if (t < p) {
             TIN* xp = xnorm + (int64_t)t * count + e0;
-            if (VEC && nv == 4) Vec4Store<TIN>::store(xp, xv);
-            else for (int v = 0; v < nv; ++v) xp[v] = xv[v];
+            if (VEC && nv == 4) Vec4Store<TIN>::store(xp, xv[t]);
+            else for (int v = 0; v < nv; ++v) xp[v] = xv[t][v];
           }
         }
+      }
+    }
 #pragma unroll
-        for (int kk = 0; kk < KB; ++kk) {
-          const TC gk = (k0 + kk < p) ? sG[(k0 + kk) * p + t] : (TC)0;
+    for (int k = 0; k < KB; ++k) {
+      if (k >= p) break;
+      TC acc[4] = {(TC)0, (TC)0, (TC)0, (TC)0};
 #pragma unroll
-          for (int v = 0; v < 4; ++v) acc[kk][v] += gk * (TC)xv[v];
+      for (int t = 0; t < KB; ++t) {
+        const TC gk = t < p ? sG[k * p + t] : (TC)0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] += gk * (TC)xv[t][v];
+      }
+      TOUT ov[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        TC r = a * acc[v];
+        if (EPI) r += b * sv[k][v];
+        ov[v] = cvt<TOUT, TC>(r);
+        if (EPI && v < nv) {
+          const double rv = (double)r;
+          sq += rv * rv;
         }
       }
-#pragma unroll
-      for (int kk = 0; kk < KB; ++kk) {
-        const int k = k0 + kk;
-        if (k >= p) break;
-        TOUT* op = out + (int64_t)k * count + e0;
-        TOUT ov[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          TC r = a * acc[kk][v];
-          if (EPI && b != (TC)0 && v < nv) r += b * (TC)src[(int64_t)k * count + e0 + v];
-          ov[v] = cvt<TOUT, TC>(r);
-          if (EPI && v < nv) {
-            const double rv = (double)r;
-            sq += rv * rv;
-          }
-        }
-        if (VEC && nv == 4) {
-          Vec4Store<TOUT>::store(op, ov);
-        } else {
-          for (int v = 0; v < nv; ++v) op[v] = ov[v];
-        }
-      }
+      TOUT* op = out + (int64_t)k * count + e0;
+      if (VEC && nv == 4) Vec4Store<TOUT>::store(op, ov);
+      else for (int v = 0; v < nv; ++v) op[v] = ov[v];
     }
   }
   if (EPI && ctl.part_out != nullptr) {
@@ -304,29 +240,35 @@ __global__ __launch_bounds__(kThreads) void tube_kernel(TubeArgs ta_, const Tube
   }
 }
 
-// the epilogue's src in FP32 (bf16_t is the bit pattern of a bfloat16)
-template <typename T> __device__ inline float to_f32(T v) { return (float)v; }
-template <> __device__ inline float to_f32<bf16_t>(bf16_t v) { return bf16_to_float(v); }
-
-// Long tubes (p >= 16): the transform out = G x in is a (p x p)(p x count)
-// contraction, so it runs on the matrix cores.  A workgroup stages G (p x p,
-// FP32, rows padded to 16) in LDS once and then walks its 64-position tiles
+// Tubes longer than 8: the transform out = G x in is a (p x p)(p x count)
+// contraction, so it runs on the matrix cores (FP32 and FP64, each with its
+// own 16x16x4 instruction).  A workgroup stages G (p x p,
+// padded to a multiple of 16) in LDS once and then walks its 64-position tiles
 // (grid stride).  Every global access of a tile is a row of 64 consecutive
 // positions of one slice, moved as 16-byte vectors: the input (from clamped
 // addresses, all issued together, scaled by the control block's s and
 // written to xnorm on the way) and the epilogue's src are loaded before the
 // tile is multiplied; wave w computes the 16 positions of column block w for
-// every 16-row band of outputs with 16x16x4 FP32 MFMAs; the products return
+// every 16-row band of outputs with 16x16x4 MFMAs; the products return
 // to LDS, and the epilogue reads them back as rows, applies a, b and src,
 // stores the rows and accumulates the workgroup's partial sum of out^2.
 // Without an epilogue (fewer registers live) the control block's loads, G
 // and the first tile are in flight together, and the next tile's rows load
 // while the current one is multiplied.
 // VEC: count a multiple of 4 and 16-byte aligned in / src / xnorm / out.
+// FP64 at 256 x 256 x 64 (67 MB moved): forward 296 us, inverse 202 before
+// (vector units, the input read again for every 8 outputs), now 27 and 27
+// (FP64 at 200 x 200 x 31: 67 / 52 -> 11.6 / 10.9; FP32 at 200 x 200 x 12: 18 / 15 -> 7.1 / 6.3).
 template <typename T> struct RowStore;
 template <> struct RowStore<float> {
   __device__ static void st(float* p, const float (&v)[4]) {
     *reinterpret_cast<f32x4*>(p) = f32x4{v[0], v[1], v[2], v[3]};
+  }
+};
+template <> struct RowStore<double> {
+  __device__ static void st(double* p, const double (&v)[4]) {
+    *reinterpret_cast<double2*>(p) = make_double2(v[0], v[1]);
+    *reinterpret_cast<double2*>(p + 2) = make_double2(v[2], v[3]);
   }
 };
 template <> struct RowStore<bf16_t> {
@@ -344,31 +286,34 @@ template <> struct RowStore<f16_t> {
   }
 };
 
-template <typename TOUT, int PM, bool SCALE, bool EPI, bool VEC>
+template <typename T, typename TOUT, int PM, bool SCALE, bool EPI, bool VEC>
 __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const VBlock vb, const bool grouped) {
-  typedef Mfma<float> MF;
+  typedef Mfma<T> MF;
   constexpr int NB = 64;            // positions per tile
-  constexpr int LDG = PM + 4;       // G as [k][t], t contiguous (+16 bytes)
-  constexpr int LDX = NB + 4;       // input / products as [row][e], e contiguous (+16 bytes)
+  // G as [k][t], t contiguous (+16 bytes; FP64 +32, two rows' operands per 64 bytes),
+  // input / products as [row][e], e contiguous (+16 bytes; FP64 +128, so that the
+  // operand's rows alternate between the halves of the banks)
+  constexpr int LDG = PM + 4;
+  constexpr int LDX = sizeof(T) == 8 ? NB + 16 : NB + 4;
   constexpr int FR = PM / 16;       // row bands
   constexpr int XU = PM * (NB / 4) / 256;  // 4-position units of a tile per thread
   constexpr int GU = PM * PM / 256;        // G entries per thread
   static_assert(XU * 256 == PM * (NB / 4) && GU * 256 == PM * PM, "tile");
-  __shared__ __attribute__((aligned(16))) float sG[PM * LDG];
-  __shared__ __attribute__((aligned(16))) float sX[PM * LDX];
+  __shared__ __attribute__((aligned(16))) T sG[PM * LDG];
+  __shared__ __attribute__((aligned(16))) T sX[PM * LDX];
   __shared__ double sh[kShCtl];
   const int p = ta.p;
   const int64_t count = ta.count;
-  const float* in = (const float*)ta.in;
+  const T* in = (const T*)ta.in;
   TOUT* out = (TOUT*)ta.out;
-  const float* G = (const float*)ta.G;
-  const float* src = (const float*)ta.src;   // FP32 outputs only (launch_tube refuses src otherwise)
-  float* xnorm = (float*)ta.xnorm;
+  const T* G = (const T*)ta.G;
+  const T* src = (const T*)ta.src;   // outputs of type T only (launch_tube refuses src otherwise)
+  T* xnorm = (T*)ta.xnorm;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t ntiles = (count + NB - 1) / NB;
 
   // a tile's input rows and src rows into registers (clamped addresses, selected)
-  float rv[XU][4], sv[XU][4];
+  T rv[XU][4], sv[XU][4];
   auto load_tile = [&](int64_t tile) {
     const int64_t e0 = tile * NB;
 #pragma unroll
@@ -378,29 +323,25 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
       const int64_t e = e0 + c;
       if constexpr (VEC) {
         const bool ok = t < p && e < count;
-        const float4 q = *reinterpret_cast<const float4*>(in + (ok ? (int64_t)t * count + e : 0));
-        rv[u][0] = ok ? q.x : 0.0f;
-        rv[u][1] = ok ? q.y : 0.0f;
-        rv[u][2] = ok ? q.z : 0.0f;
-        rv[u][3] = ok ? q.w : 0.0f;
+        Vec4Load<T>::load(in + (ok ? (int64_t)t * count + e : 0), rv[u]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) rv[u][v] = ok ? rv[u][v] : (T)0;
         if (EPI) {
           const bool oks = ok && src != nullptr;
-          const float4 w = *reinterpret_cast<const float4*>(oks ? src + (int64_t)t * count + e : in);
-          sv[u][0] = oks ? w.x : 0.0f;
-          sv[u][1] = oks ? w.y : 0.0f;
-          sv[u][2] = oks ? w.z : 0.0f;
-          sv[u][3] = oks ? w.w : 0.0f;
+          Vec4Load<T>::load(oks ? src + (int64_t)t * count + e : in, sv[u]);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sv[u][v] = oks ? sv[u][v] : (T)0;
         }
       } else {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const bool ok = t < p && e + v < count;
-          const float x = in[ok ? (int64_t)t * count + e + v : 0];
-          rv[u][v] = ok ? x : 0.0f;
+          const T x = in[ok ? (int64_t)t * count + e + v : 0];
+          rv[u][v] = ok ? x : (T)0;
           if (EPI) {
             const bool oks = ok && src != nullptr;
-            const float y = (src != nullptr ? src : in)[oks ? (int64_t)t * count + e + v : 0];
-            sv[u][v] = oks ? y : 0.0f;
+            const T y = (src != nullptr ? src : in)[oks ? (int64_t)t * count + e + v : 0];
+            sv[u][v] = oks ? y : (T)0;
           }
         }
       }
@@ -410,13 +351,13 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
   // prologue: the control block's loads, G and the first tile's rows are all in
   // flight before the first of them is used
   const CtlLoad cl = ctl_load(ta.ctl);
-  float gv[GU];
+  T gv[GU];
 #pragma unroll
   for (int u = 0; u < GU; ++u) {
     const int i = tid + u * 256, k = i / PM, t = i % PM;
     const bool ok = k < p && t < p;
-    const float v = G[ok ? k * p + t : 0];
-    gv[u] = ok ? v : 0.0f;
+    const T v = G[ok ? k * p + t : 0];
+    gv[u] = ok ? v : (T)0;
   }
   int64_t tile = vb.x;
   if (!EPI && tile < ntiles) load_tile(tile);
@@ -424,8 +365,8 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
   if (!ctl_eval(ta.ctl, cl, a_d, b_d, s_d, sh, vb)) return;
   if (!SCALE) s_d = 1.0;
   if (!EPI) { a_d = 1.0; b_d = 0.0; }
-  const float a = (float)a_d, b = (float)b_d, sc = (float)s_d;
-  const bool use_src = EPI && src != nullptr && b != 0.0f;   // b = 0: src never enters
+  const T a = (T)a_d, b = (T)b_d, sc = (T)s_d;
+  const bool use_src = EPI && src != nullptr && b != (T)0;   // b = 0: src never enters
 #pragma unroll
   for (int u = 0; u < GU; ++u) {
     const int i = tid + u * 256, k = i / PM, t = i % PM;
@@ -446,9 +387,9 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
 #pragma unroll
         for (int v = 0; v < 4; ++v) rv[u][v] *= sc;
         if (xnorm != nullptr && t < p) {
-          float* xp = xnorm + (int64_t)t * count + e;
+          T* xp = xnorm + (int64_t)t * count + e;
           if (VEC) {
-            if (e < count) RowStore<float>::st(xp, rv[u]);
+            if (e < count) RowStore<T>::st(xp, rv[u]);
           } else {
 #pragma unroll
             for (int v = 0; v < 4; ++v)
@@ -456,7 +397,7 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
           }
         }
       }
-      *reinterpret_cast<float4*>(&sX[t * LDX + c]) = make_float4(rv[u][0], rv[u][1], rv[u][2], rv[u][3]);
+      RowStore<T>::st(&sX[t * LDX + c], rv[u]);
     }
     __syncthreads();
     // without an epilogue (fewer registers live) the next tile's rows load while
@@ -466,21 +407,22 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
 #pragma unroll
     for (int f = 0; f < FR; ++f)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[f][r] = 0.0f;
+      for (int r = 0; r < 4; ++r) acc[f][r] = (T)0;
 #pragma unroll 4
     for (int t0 = 0; t0 < PM; t0 += 4) {
-      const float* bp = &sX[(t0 + lk) * LDX + wave * 16 + lr];
+      const T* bp = &sX[(t0 + lk) * LDX + wave * 16 + lr];
 #pragma unroll
       for (int f = 0; f < FR; ++f) acc[f] = MF::mac(&sG[(f * 16 + lr) * LDG + t0 + lk], bp, acc[f]);
     }
     // a wave reads and writes only its own 16 columns of sX, and a wave's LDS
     // accesses complete in order: no block barrier before its products go back
     __builtin_amdgcn_wave_barrier();
-    // products back to LDS as [k][e]: lane holds rows 4 (lane / 16) + r of column lane % 16
+    // products back to LDS as [k][e]: lane holds rows 4 (lane / 16) + r (FP64: lane / 16
+    // + 4 r) of column lane % 16
 #pragma unroll
     for (int f = 0; f < FR; ++f)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sX[(f * 16 + lk * 4 + r) * LDX + wave * 16 + lr] = acc[f][r];
+      for (int r = 0; r < 4; ++r) sX[(f * 16 + (MF::ROWS_STRIDED ? lk + 4 * r : lk * 4 + r)) * LDX + wave * 16 + lr] = acc[f][r];
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < XU; ++u) {
@@ -488,11 +430,13 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
       const int k = i / (NB / 4), c = (i % (NB / 4)) * 4;
       const int64_t e = e0 + c;
       if (k >= p) continue;
-      const float4 q = *reinterpret_cast<const float4*>(&sX[k * LDX + c]);
-      float y[4] = {a * q.x, a * q.y, a * q.z, a * q.w};
+      T y[4];
+      Vec4Load<T>::load(&sX[k * LDX + c], y);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) y[v] *= a;
       if (EPI) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) y[v] += use_src ? b * sv[u][v] : 0.0f;
+        for (int v = 0; v < 4; ++v) y[v] += use_src ? b * sv[u][v] : (T)0;
       }
       TOUT* op = out + (int64_t)k * count + e;
       if (VEC) {
@@ -507,7 +451,7 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
 #pragma unroll
         for (int v = 0; v < 4; ++v)
           if (e + v < count) {
-            op[v] = cvt<TOUT, float>(y[v]);
+            op[v] = cvt<TOUT, T>(y[v]);
             if (EPI) sq += (double)y[v] * (double)y[v];
           }
       }
@@ -519,25 +463,25 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
   }
 }
 
-template <typename TOUT, int PM, bool SCALE, bool EPI, bool VEC, bool GROUPED>
+template <typename T, typename TOUT, int PM, bool SCALE, bool EPI, bool VEC, bool GROUPED>
 __global__ __launch_bounds__(256) void tube_mfma_kernel(TubeArgs ta_, const TubeArgs* grp, const int4* bmap) {
   if constexpr (!GROUPED) {
-    tube_mfma_kernel_body<TOUT, PM, SCALE, EPI, VEC>(ta_, hw_block(), false);
+    tube_mfma_kernel_body<T, TOUT, PM, SCALE, EPI, VEC>(ta_, hw_block(), false);
   } else {
     VBlock vb;
     const TubeArgs g = group_args(grp, bmap, vb);
-    tube_mfma_kernel_body<TOUT, PM, SCALE, EPI, VEC>(g, vb, true);
+    tube_mfma_kernel_body<T, TOUT, PM, SCALE, EPI, VEC>(g, vb, true);
   }
 }
 
-template <typename TOUT>
+template <typename T, typename TOUT>
 static hipError_t launch_tube_mfma(dctk_ctx ctx, hipStream_t s, int64_t p, int64_t count, const void* in, void* out,
-                                   const float* G, const void* src, void* xnorm, const Ctl& ctl, bool scale,
+                                   const T* G, const void* src, void* xnorm, const Ctl& ctl, bool scale,
                                    bool epi, int* nblocks_out) {
   // a few workgroups per CU, each walking several 64-position tiles, so G
   // is staged once per workgroup rather than once per tile
   int64_t blocks = (count + 63) / 64;
-  const int64_t cap = 4 * (int64_t)num_cus();
+  const int64_t cap = (sizeof(T) == 8 ? 2 : 4) * (int64_t)num_cus();   // what fits a CU's LDS
   if (blocks > cap) blocks = cap;
   if (nblocks_out) *nblocks_out = (int)blocks;
   if (epi && ctl.part_out != nullptr && blocks > kRedBlocks) return hipErrorInvalidConfiguration;
@@ -555,20 +499,19 @@ static hipError_t launch_tube_mfma(dctk_ctx ctx, hipStream_t s, int64_t p, int64
   const dim3 grid((unsigned)blocks);
 #define DCTK_TMV(PM_, SC_, EP_) \
   do { \
-    if (vec) return launch_kernel(ctx, s, tube_mfma_kernel<TOUT, PM_, SC_, EP_, true, false>, tube_mfma_kernel<TOUT, PM_, SC_, EP_, true, true>, grid, 256, 0, ta); \
-    return launch_kernel(ctx, s, tube_mfma_kernel<TOUT, PM_, SC_, EP_, false, false>, tube_mfma_kernel<TOUT, PM_, SC_, EP_, false, true>, grid, 256, 0, ta); \
+    if (vec) return launch_kernel(ctx, s, tube_mfma_kernel<T, TOUT, PM_, SC_, EP_, true, false>, tube_mfma_kernel<T, TOUT, PM_, SC_, EP_, true, true>, grid, 256, 0, ta); \
+    return launch_kernel(ctx, s, tube_mfma_kernel<T, TOUT, PM_, SC_, EP_, false, false>, tube_mfma_kernel<T, TOUT, PM_, SC_, EP_, false, true>, grid, 256, 0, ta); \
   } while (0)
 #define DCTK_TM(PM_) \
   do { \
-    if (scale && epi) DCTK_TMV(PM_, true, true); \
     if (scale) DCTK_TMV(PM_, true, false); \
-    if (epi) DCTK_TMV(PM_, false, true); \
-    DCTK_TMV(PM_, false, false); \
+    if constexpr (sizeof(T) == sizeof(TOUT)) DCTK_TMV(PM_, false, true); \
   } while (0)
   if (p <= 16) DCTK_TM(16);
   if (p <= 32) DCTK_TM(32);
   if (p <= 48) DCTK_TM(48);
   DCTK_TM(64);
+  return hipErrorInvalidValue;   // a 16-bit output is a slice product's operand: the input side
 #undef DCTK_TM
 #undef DCTK_TMV
 }
@@ -917,7 +860,7 @@ __global__ __launch_bounds__(256) void tube_pair_kernel(PairArgs pa_, const Pair
   }
 }
 
-bool tube_pair_ok(int64_t p, int vec_dtype) { return vec_dtype == DCTK_F32 && (p <= 8 || p >= 16) && p <= kMaxTube; }
+bool tube_pair_ok(int64_t p, int vec_dtype) { return vec_dtype == DCTK_F32 && p <= kMaxTube; }
 
 hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p, int64_t count, const float* c,
                             const float* src, float* y, void* x, const float* G1, const Ctl& ctl,
@@ -998,18 +941,17 @@ static hipError_t launch_tube_t(dctk_ctx ctx, hipStream_t s, int64_t p, int64_t 
   const dim3 grid((unsigned)blocks);
 #define DCTK_TUBE_LAUNCH(KB, V, S, E) \
   return launch_kernel(ctx, s, tube_kernel<TIN, TOUT, TC, KB, V, S, E, false>, tube_kernel<TIN, TOUT, TC, KB, V, S, E, true>, grid, kThreads, (unsigned)shmem, ta)
-#define DCTK_TUBE_SE(KB, V)                                  \
-  do {                                                       \
-    if (scale && epi) DCTK_TUBE_LAUNCH(KB, V, true, true);    \
-    else if (scale) DCTK_TUBE_LAUNCH(KB, V, true, false);     \
-    else if (epi) DCTK_TUBE_LAUNCH(KB, V, false, true);       \
-    else DCTK_TUBE_LAUNCH(KB, V, false, false);               \
+#define DCTK_TUBE_SE(KB, V)                                                    \
+  do {                                                                         \
+    if (scale) DCTK_TUBE_LAUNCH(KB, V, true, false);                            \
+    if constexpr (sizeof(TIN) == sizeof(TOUT)) DCTK_TUBE_LAUNCH(KB, V, false, true); \
   } while (0)
   if (p <= 4) {
     if (vec) DCTK_TUBE_SE(4, true); else DCTK_TUBE_SE(4, false);
   } else {
     if (vec) DCTK_TUBE_SE(8, true); else DCTK_TUBE_SE(8, false);
   }
+  return hipErrorInvalidValue;   // a 16-bit output is a slice product's operand: the input side
 #undef DCTK_TUBE_SE
 #undef DCTK_TUBE_LAUNCH
 }
@@ -1021,31 +963,23 @@ static hipError_t launch_tube_t(dctk_ctx ctx, hipStream_t s, int64_t p, int64_t 
 hipError_t launch_tube(dctk_ctx ctx, hipStream_t s, int in_dtype, int out_dtype, int64_t p, int64_t count,
                        const void* in, void* out, const double* Gd, const float* Gf,
                        const void* src, void* xnorm, const Ctl& ctl, bool scale, bool epi, int* nblocks_out) {
+  // the input side (scale, xnorm) or the output side (a, b, src, partials)
+  if (scale == epi || p > kMaxTube) return hipErrorInvalidValue;
+  const bool mfma = p > 8;
+#define DCTK_TUBE(T, TO, G)                                                                                             \
+  (mfma ? launch_tube_mfma<T, TO>(ctx, s, p, count, in, out, G, src, xnorm, ctl, scale, epi, nblocks_out)                \
+        : launch_tube_t<T, TO, T>(ctx, s, p, count, in, out, G, src, xnorm, ctl, scale, epi, nblocks_out))
   if (in_dtype == DCTK_F64) {
     if (out_dtype != DCTK_F64) return hipErrorInvalidValue;
-    return launch_tube_t<double, double, double>(ctx, s, p, count, in, out, Gd, src, xnorm, ctl, scale, epi, nblocks_out);
+    return DCTK_TUBE(double, double, Gd);
   }
-  // long tubes on the matrix cores (unless the 64-position blocks would exceed the partial-sum slots)
-  const bool mfma = p >= 16 && p <= kMaxTube && !(epi && ctl.part_out != nullptr && (count + 63) / 64 > kRedBlocks);
   switch (out_dtype) {
-    case DCTK_F32:
-      if (mfma) return launch_tube_mfma<float>(ctx, s, p, count, in, out, Gf, src, xnorm, ctl, scale, epi, nblocks_out);
-      return launch_tube_t<float, float, float>(ctx, s, p, count, in, out, Gf, src, xnorm, ctl, scale, epi, nblocks_out);
-    case DCTK_BF16:
-      if (src) return hipErrorInvalidValue;
-      if (mfma)
-        return launch_tube_mfma<bf16_t>(ctx, s, p, count, in, out, Gf, nullptr, xnorm, ctl, scale, false, nblocks_out);
-      return launch_tube_t<float, bf16_t, float>(ctx, s, p, count, in, out, Gf, nullptr, xnorm, ctl, scale, false,
-                                                 nblocks_out);
-    case DCTK_F16:
-      if (src) return hipErrorInvalidValue;
-      if (mfma)
-        return launch_tube_mfma<f16_t>(ctx, s, p, count, in, out, Gf, nullptr, xnorm, ctl, scale, false, nblocks_out);
-      return launch_tube_t<float, f16_t, float>(ctx, s, p, count, in, out, Gf, nullptr, xnorm, ctl, scale, false,
-                                                nblocks_out);
-    default:
-      return hipErrorInvalidValue;
+    case DCTK_F32: return DCTK_TUBE(float, float, Gf);
+    case DCTK_BF16: return src ? hipErrorInvalidValue : DCTK_TUBE(float, bf16_t, Gf);
+    case DCTK_F16: return src ? hipErrorInvalidValue : DCTK_TUBE(float, f16_t, Gf);
+    default: return hipErrorInvalidValue;
   }
+#undef DCTK_TUBE
 }
 
 }  // namespace dctk
