@@ -21,7 +21,9 @@
 // A workgroup owns NB = E / p neighbouring tubes (E = 4096 FP32 or 2048 FP64
 // elements): it loads the p x NB block row by row (NB consecutive positions
 // of each slice), runs every step in LDS and writes the block back, so each
-// element crosses HBM once each way.  Workgroups stay resident and loop over
+// element crosses HBM once each way (this is the kernel of p < 128, p > 1024
+// and 16-bit results; the lengths between keep the FFT in registers, below).
+// Workgroups stay resident and loop over
 // blocks of tubes, loading the next block into registers while the current
 // one is transformed; the row constants (rotations, diagonals) and the FFT
 // twiddles are computed once per workgroup.  The work is HBM-bound: about
@@ -411,6 +413,448 @@ __global__ __launch_bounds__(kFastThreads, 4) void tube_fast_kernel(FastArgs a_,
   }
 }
 
+// ---- the same transforms with the FFT in registers ------------------------
+// Tubes of 128 to 1024 positions.  A thread holds 16 complex values, so the
+// FFT of p = 16 R2 Q is three exchanges through LDS instead of one per pair of
+// radix-2 stages: radix 16 over n1 (n = n1 M + r, M = R2 Q), radix R2 over r1
+// (r = r1 Q + r2), radix Q over r2 merged with the step that separates the two
+// tubes; k = k1 + 16 k2 + B k3 with B = 16 R2.  The inverse runs the same
+// steps backwards.  Each pass reads and writes the same LDS slots, so one
+// buffer serves all of them.  Tubes 2c and 2c + 1 are the real and imaginary
+// parts of complex column c: every global access is a pair of values, and a
+// tile is 32 positions (64 for p = 128; half that in FP64), whole 128-byte
+// lines.  The (I + Z) family works on rows held in registers (a thread loads
+// or stores 16 consecutive rows); its scans cross a wave by shuffles and the
+// workgroup by one exchange.
+// Workgroups of 1024 (FP64 512) threads in all fill a CU, with 36 to 39 KB of
+// LDS per 256 (128) and 128 (256) registers a thread, each with its next tile
+// in flight.  What bounds it is HBM in rows of one line per slice: copying the
+// tiles without the transform takes 120 to 128 us at p = 256, 512 x 512
+// positions, FP32 (537 MB).  The LDS kernel waited on its 8 to 10 barriers per 16
+// KB block and moved 32-byte pieces of lines from p = 512 on.  us before ->
+// now, M / M^{-1} (the others lie between or below):
+//   p = 128,  2^18 positions  FP32  77 / 109 ->  57 /  53   FP64  145 /  205 -> 123 / 124
+//   p = 256,  2^18            FP32 216 / 274 -> 146 / 148   FP64  448 /  598 -> 298 / 297
+//   p = 512,  2^17            FP32 318 / 360 -> 148 / 152   FP64  646 /  801 -> 256 / 244
+//   p = 1024, 2^16            FP32 583 / 643 -> 151 / 161   FP64 1208 / 1376 -> 303 / 273
+template <typename R, int P>
+struct RegCfg {
+  static constexpr int T = (P <= 256 ? 256 : P) * 4 / (int)sizeof(R);  // threads
+  static constexpr int R2 = P == 128 ? 8 : 16;          // second radix
+  static constexpr int Q = P / (16 * R2);               // third radix
+  static constexpr int M = R2 * Q;
+  static constexpr int B = 16 * R2;
+  static constexpr int C = 16 * T / P;                  // complex columns of a tile
+  static constexpr int NB = 2 * C;                      // positions of a tile
+  static constexpr int NP = 8 / Q;                      // base pairs (b, B - b) of a thread
+  static constexpr int NW = T / 64;
+  static constexpr int WAVES = 16 / (int)sizeof(R);  // per SIMD: 128 (256) registers a thread
+  static constexpr int PER_CU = 256 * WAVES / T;
+};
+
+template <typename R> struct Two { R x, y; };                          // two values at an R's alignment
+template <typename R> struct alignas(2 * sizeof(R)) Cplx { R x, y; };  // a complex number
+
+// a times w, or times conj(w) for the inverse
+template <bool INV, typename R>
+__device__ inline Cplx<R> twid(Cplx<R> a, Cplx<R> w) {
+  return INV ? Cplx<R>{a.x * w.x + a.y * w.y, a.y * w.x - a.x * w.y}
+             : Cplx<R>{a.x * w.x - a.y * w.y, a.x * w.y + a.y * w.x};
+}
+// 4 points in place, natural order, exp(-+2 pi i / 4)
+template <bool INV, typename R>
+__device__ inline void fft4(Cplx<R>& a, Cplx<R>& b, Cplx<R>& c, Cplx<R>& d) {
+  typedef Cplx<R> C2;
+  const C2 s{a.x + c.x, a.y + c.y}, t{a.x - c.x, a.y - c.y}, u{b.x + d.x, b.y + d.y};
+  const C2 v = INV ? C2{d.y - b.y, b.x - d.x} : C2{b.y - d.y, d.x - b.x};
+  a = C2{s.x + u.x, s.y + u.y};
+  b = C2{t.x + v.x, t.y + v.y};
+  c = C2{s.x - u.x, s.y - u.y};
+  d = C2{t.x - v.x, t.y - v.y};
+}
+// N points of z in place; output k is z[fft_at<N>(k)]
+template <int N>
+__device__ constexpr int fft_at(int k) {
+  return N == 16 ? 4 * (k & 3) + (k >> 2) : N == 8 ? 4 * (k & 1) + (k >> 1) : k;
+}
+template <int N, bool INV, typename R>
+__device__ inline void fftr(Cplx<R>* z) {
+  typedef Cplx<R> C2;
+  constexpr R c1 = (R)0.92387953251128674, s1 = (R)0.38268343236508977, h = (R)0.70710678118654752;
+  if constexpr (N == 2) {
+    const C2 a = z[0], b = z[1];
+    z[0] = C2{a.x + b.x, a.y + b.y};
+    z[1] = C2{a.x - b.x, a.y - b.y};
+  } else if constexpr (N == 4) {
+    fft4<INV>(z[0], z[1], z[2], z[3]);
+  } else if constexpr (N == 8) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const C2 u = z[b], v = z[b + 4];
+      z[b] = C2{u.x + v.x, u.y + v.y};
+      z[b + 4] = C2{u.x - v.x, u.y - v.y};
+    }
+    z[5] = twid<INV>(z[5], C2{h, -h});
+    z[6] = INV ? C2{-z[6].y, z[6].x} : C2{z[6].y, -z[6].x};
+    z[7] = twid<INV>(z[7], C2{-h, -h});
+    fft4<INV>(z[0], z[1], z[2], z[3]);
+    fft4<INV>(z[4], z[5], z[6], z[7]);
+  } else if constexpr (N == 16) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) fft4<INV>(z[b], z[b + 4], z[b + 8], z[b + 12]);
+    z[5] = twid<INV>(z[5], C2{c1, -s1});
+    z[6] = twid<INV>(z[6], C2{h, -h});
+    z[7] = twid<INV>(z[7], C2{s1, -c1});
+    z[9] = twid<INV>(z[9], C2{h, -h});
+    z[10] = INV ? C2{-z[10].y, z[10].x} : C2{z[10].y, -z[10].x};
+    z[11] = twid<INV>(z[11], C2{-h, -h});
+    z[13] = twid<INV>(z[13], C2{s1, -c1});
+    z[14] = twid<INV>(z[14], C2{-h, -h});
+    z[15] = twid<INV>(z[15], C2{-c1, s1});
+#pragma unroll
+    for (int a = 0; a < 16; a += 4) fft4<INV>(z[a], z[a + 1], z[a + 2], z[a + 3]);
+  }
+}
+
+template <typename R, int P, bool INV, bool SCALE, bool EPI>
+__device__ __forceinline__ void tube_reg_body(const FastArgs& a, const VBlock vb) {
+  static_assert(!(SCALE && INV) && !(EPI && !INV), "the input side precedes F, the output side follows F^{-1}");
+  typedef RegCfg<R, P> G;
+  typedef Two<R> F2;
+  typedef Cplx<R> C2;
+  constexpr int T = G::T, R2 = G::R2, Q = G::Q, M = G::M, B = G::B, C = G::C, NP = G::NP, NW = G::NW;
+  __shared__ C2 buf[P * C];
+  __shared__ C2 tw[P / 2];       // exp(-2 pi i m / p)
+  __shared__ C2 rot[P / 2 + 1];  // cos, sin of pi k / (2p)
+  __shared__ R dg[P];            // diagonal
+  __shared__ C2 part[NW * C];
+  __shared__ double shc[EPI ? 2 * (NW + 1) : SCALE ? 2 * (NW + 1) : 1];  // the control block's reductions
+  const R* in = (const R*)a.in;
+  R* out = (R*)a.out;
+  const int tid = threadIdx.x;
+  CtlLoad cl{};
+  if constexpr (SCALE || EPI) cl = ctl_load(a.ctl);
+  const int64_t count = a.count;
+  const int64_t ntiles = (count + G::NB - 1) / G::NB;
+  const int jc = tid % C, wave = tid >> 6, lane = tid & 63;
+  int g = tid / C;
+  const int pre = a.pre, post = a.post;
+  // LDS slot of (row block x of M, element y) of column jc: neighbouring x lie
+  // in the two halves of the banks
+  auto at = [&](int x, int y) { return (x * M + (C < 32 ? y ^ (x & 1) : y)) * C + jc; };
+  // exp(-2 pi i m / p), 0 <= m < p, and cos, sin of pi k / (2p), 0 <= k < p, from half tables
+  auto w_p = [&](int m) {
+    const C2 w = tw[m & (P / 2 - 1)];
+    return m & (P / 2) ? C2{-w.x, -w.y} : w;
+  };
+  auto rot_at = [&](int k) {
+    const bool up = k > P / 2;
+    const C2 w = rot[up ? P - k : k];
+    return up ? C2{w.y, w.x} : w;
+  };
+  // FFT position of row t: even rows first, odd ones reversed after them
+  auto pos = [](int t) { return (t & 1) ? P - 1 - (t >> 1) : t >> 1; };
+
+  // the 16 rows of a thread: forward 16 g + i; inverse the base pairs'
+  // (b = g + 16 R2 / (2 NP) u, then B - b or B / 2), k3 = 0 .. Q - 1
+  auto base = [&](int u, int half) {
+    const int b = g + (T / C) * u;
+    return half ? (b ? B - b : B / 2) : b;
+  };
+  auto row_in = [&](int i) {
+    if constexpr (!INV) return 16 * g + i;
+    else return base(i / (2 * Q), (i / Q) & 1) + B * (i % Q);
+  };
+  F2 x[16], xe{(R)0, (R)0};  // xe: the row after a wave's last (forward (I + Z) only)
+  // pointer to row_in(i) (rows of the second base of a pair run backwards)
+  auto in_ptr = [&](int i) {
+    if constexpr (!INV) {
+      return in + (int64_t)(16 * g) * count + i * count;
+    } else {
+      const int u = i / (2 * Q), half = (i / Q) & 1, k3 = i % Q;
+      if (!half) return in + (int64_t)g * count + ((T / C) * u + B * k3) * count;
+      if (u == 0) return in + (int64_t)base(0, 1) * count + B * k3 * count;
+      return in + (int64_t)(B - g) * count + (B * k3 - (T / C) * u) * count;
+    }
+  };
+  auto get = [&](const R* s, int64_t e, bool full) {
+    if (full) return *reinterpret_cast<const F2*>(s + e);
+    return F2{s[e < count ? e : count - 1], s[e + 1 < count ? e + 1 : count - 1]};  // tail: clamped
+  };
+  auto put = [&](R* d, int64_t e, bool full, F2 v) {
+    if (full) {
+      *reinterpret_cast<F2*>(d + e) = v;
+    } else {
+      if (e < count) d[e] = v.x;
+      if (e + 1 < count) d[e + 1] = v.y;
+    }
+  };
+  auto fetch = [&](int64_t tile) {
+    const int64_t e = tile * G::NB + 2 * jc;
+    const bool full = (tile + 1) * G::NB <= count;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) x[i] = get(in_ptr(i), e, full);
+    if (!INV && pre == 1 && lane >= 64 - C) xe = get(in + (int64_t)(16 * g + 16 < P ? 16 * g + 16 : P - 1) * count, e, full);
+  };
+  const int grp = a.group;
+  auto tile_of = [&](int64_t n) { return ((int64_t)vb.x + n / grp * a.gx) * grp + n % grp; };
+  int64_t n = 0, tile = tile_of(0);
+  fetch(tile);
+  for (int k = tid; k < P; k += T) {
+    R s, c;
+    sc_pi((R)(2 * k) / (R)P, &s, &c);
+    if (k < P / 2) tw[k] = C2{c, -s};
+    sc_pi((R)k / (R)(2 * P), &s, &c);
+    if (k <= P / 2) rot[k] = C2{c, s};
+    dg[k] = fast_scale<R>(a.scale, k, P, c);
+  }
+  R sc = 1, ea = 1, eb = 0;
+  bool use_src = false;
+  if constexpr (SCALE || EPI) {
+    double ad, bd, sd;
+    if (!ctl_eval(a.ctl, cl, ad, bd, sd, shc, vb)) return;
+    if (SCALE) sc = (R)sd;
+    if (EPI) {
+      ea = (R)ad;
+      eb = (R)bd;
+      use_src = a.src != nullptr && bd != 0.0;  // b = 0: src never enters
+    }
+  }
+  R* xn = (R*)a.xnorm;
+  const R* sp = use_src ? (const R*)a.src : in;
+  double sq = 0.0;
+  // alternating scan of this thread's 16 rows v (first row even): v_i = sum of
+  // (-1)^(t - i) y_t over rows t <= i (prefix) or t >= i (suffix) of the tube
+  auto scan = [&](F2* v, bool suffix) {
+    F2 run{(R)0, (R)0};
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int i = suffix ? 15 - q : q;
+      run.x += (i & 1) ? -v[i].x : v[i].x;
+      run.y += (i & 1) ? -v[i].y : v[i].y;
+      v[i] = run;
+    }
+    F2 s = run;
+#pragma unroll
+    for (int d = C; d < 64; d <<= 1) {
+      const R ux = suffix ? __shfl_down(s.x, d) : __shfl_up(s.x, d);
+      const R uy = suffix ? __shfl_down(s.y, d) : __shfl_up(s.y, d);
+      const bool ok = suffix ? lane + d < 64 : lane >= d;
+      s.x += ok ? ux : (R)0;
+      s.y += ok ? uy : (R)0;
+    }
+    if (suffix ? lane < C : lane >= 64 - C) part[wave * C + jc] = C2{s.x, s.y};
+    F2 o{suffix ? __shfl_down(s.x, C) : __shfl_up(s.x, C), suffix ? __shfl_down(s.y, C) : __shfl_up(s.y, C)};
+    if (suffix ? lane + C >= 64 : lane < C) o = F2{(R)0, (R)0};
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+      if (suffix ? w > wave : w < wave) {
+        o.x += part[w * C + jc].x;
+        o.y += part[w * C + jc].y;
+      }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      v[i].x += o.x;
+      v[i].y += o.y;
+      if (i & 1) v[i] = F2{-v[i].x, -v[i].y};
+    }
+  };
+  // radix 16 over the slots (x = 0 .. 15, r)
+  auto pass16 = [&]() {
+    C2 z[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z[i] = buf[at(i, g)];
+    fftr<16, INV>(z);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const C2 v = z[fft_at<16>(i)];
+      buf[at(i, g)] = INV || i == 0 ? v : twid<INV>(v, w_p(g * i));
+    }
+  };
+  // radix R2 over the slots (k1, y Q + r2)
+  auto passr2 = [&]() {
+#pragma unroll
+    for (int w = 0; w < 16 / R2; ++w) {
+      const int item = g + w * (T / C);
+      const int k1 = item / Q, r2 = item % Q;
+      C2 z[R2];
+#pragma unroll
+      for (int i = 0; i < R2; ++i) z[i] = buf[at(k1, i * Q + r2)];
+      fftr<R2, INV>(z);
+#pragma unroll
+      for (int i = 0; i < R2; ++i) {
+        C2 v = z[fft_at<R2>(i)];
+        if constexpr (INV) v = twid<true>(v, w_p((i * Q + r2) * k1));
+        else if constexpr (Q > 1) v = twid<false>(v, w_p(16 * r2 * i));
+        buf[at(k1, i * Q + r2)] = v;
+      }
+    }
+  };
+  __syncthreads();  // the tables
+  for (; tile < ntiles; tile = tile_of(++n)) {
+    // g is opaque in each turn: what derives from it (table entries, row
+    // addresses) is computed again, not held in registers over the loop
+    asm volatile("" : "+v"(g));
+    const int64_t e = tile * G::NB + 2 * jc;
+    const bool full = (tile + 1) * G::NB <= count;
+    const bool live0 = e < count, live1 = e + 1 < count;
+    if constexpr (!INV) {
+      if constexpr (SCALE) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          x[i] = F2{sc * x[i].x, sc * x[i].y};
+          if (xn != nullptr) put(xn + (int64_t)(16 * g) * count + i * count, e, full, x[i]);
+        }
+        xe = F2{sc * xe.x, sc * xe.y};
+      }
+      if (pre == 1) {
+        const F2 dn{__shfl_down(x[0].x, C), __shfl_down(x[0].y, C)};
+        xe = lane < 64 - C ? dn : 16 * g + 16 < P ? xe : F2{(R)0, (R)0};
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const F2 nx = i < 15 ? x[i + 1] : xe;
+          x[i] = F2{x[i].x + nx.x, x[i].y + nx.y};
+        }
+      } else if (pre == 2) {
+        scan(x, false);
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int m = pos(16 * g + i);
+        buf[at(m / M, m % M)] = C2{x[i].x, x[i].y};
+      }
+    } else {
+      // Z_k = V_k(tube 2c) + i V_k(tube 2c + 1),
+      // V_k = exp(i pi k / (2p)) (X_k - i X_{p-k}), X_p = 0, with X = R x
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const R q = dg[row_in(i)];
+        x[i] = F2{q * x[i].x, q * x[i].y};
+      }
+#pragma unroll
+      for (int u = 0; u < NP; ++u) {
+        const bool b0 = base(u, 0) == 0;
+        const F2 *xb = x + 2 * Q * u, *xp = xb + Q;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          const int b = base(u, half);
+          C2 z[Q];
+#pragma unroll
+          for (int k3 = 0; k3 < Q; ++k3) {
+            const F2 v = half ? xp[k3] : xb[k3];
+            F2 m;  // X_{p-k}
+            if (half) {
+              m = b0 ? xp[Q - 1 - k3] : xb[Q - 1 - k3];
+            } else {
+              const F2 s = k3 ? xb[Q - k3] : F2{(R)0, (R)0};
+              m = b0 ? s : xp[Q - 1 - k3];
+            }
+            const C2 w = rot_at(b + B * k3);
+            z[k3] = C2{w.x * v.x + w.y * m.x - (w.y * v.y - w.x * m.y),
+                       w.y * v.x - w.x * m.x + (w.x * v.y + w.y * m.y)};
+          }
+          fftr<Q, true>(z);
+#pragma unroll
+          for (int r2 = 0; r2 < Q; ++r2)
+            buf[at(b % 16, b / 16 * Q + r2)] = r2 ? twid<true>(z[r2], w_p(16 * r2 * (b / 16))) : z[r2];
+        }
+      }
+    }
+    const int64_t next = tile_of(n + 1);
+    __syncthreads();
+    fetch(next < ntiles ? next : tile);  // in flight while this tile is transformed
+    if constexpr (!INV) {
+      pass16();
+      __syncthreads();
+      passr2();
+      __syncthreads();
+      // the two tubes' spectra from Z_k and Z_{p-k}; F_k = Re(exp(-i pi k / (2p)) V_k), then the diagonal
+#pragma unroll
+      for (int u = 0; u < NP; ++u) {
+        const bool b0 = base(u, 0) == 0;
+        C2 z[2][Q];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          const int b = base(u, half);
+#pragma unroll
+          for (int r2 = 0; r2 < Q; ++r2) z[half][r2] = buf[at(b % 16, b / 16 * Q + r2)];
+          fftr<Q, false>(z[half]);
+        }
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+          for (int k3 = 0; k3 < Q; ++k3) {
+            const int k = base(u, half) + B * k3;
+            const C2 v = z[half][k3];
+            const C2 s = half ? z[1][Q - 1 - k3] : z[0][(Q - k3) % Q], o = z[1 - half][Q - 1 - k3];
+            const C2 m = b0 ? s : o;
+            const C2 w = rot_at(k);
+            const R q = (R)0.5 * dg[k];
+            put(out + (int64_t)k * count, e, full,
+                F2{((v.x + m.x) * w.x + (v.y - m.y) * w.y) * q, ((v.y + m.y) * w.x + (m.x - v.x) * w.y) * q});
+          }
+      }
+      __syncthreads();
+    } else {
+      passr2();
+      __syncthreads();
+      pass16();
+      __syncthreads();
+      // rows 16 g .. 16 g + 15: y_t = v_n / p with n the position of t
+      F2 y[16];
+      constexpr R inv_p = (R)1 / (R)P;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int m = pos(16 * g + i);
+        const C2 v = buf[at(m / M, m % M)];
+        y[i] = F2{v.x * inv_p, v.y * inv_p};
+      }
+      if (post == 2) {
+        scan(y, true);  // its barrier follows every read of buf
+      } else {
+        if (post == 1) {
+          const int m = pos(16 * g - 1 > 0 ? 16 * g - 1 : 0);
+          const C2 v = buf[at(m / M, m % M)];
+#pragma unroll
+          for (int i = 15; i > 0; --i) y[i] = F2{y[i].x + y[i - 1].x, y[i].y + y[i - 1].y};
+          if (g > 0) y[0] = F2{y[0].x + v.x * inv_p, y[0].y + v.y * inv_p};
+        }
+        __syncthreads();
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        if constexpr (EPI) {
+          const F2 sv = get(sp + (int64_t)(16 * g) * count + i * count, e, full);
+          y[i].x = ea * y[i].x + (use_src ? eb * sv.x : (R)0);
+          y[i].y = ea * y[i].y + (use_src ? eb * sv.y : (R)0);
+          if (live0) sq += (double)y[i].x * (double)y[i].x;
+          if (live1) sq += (double)y[i].y * (double)y[i].y;
+        }
+        put(out + (int64_t)(16 * g) * count + i * count, e, full, y[i]);
+      }
+    }
+  }
+  if constexpr (EPI) {
+    if (a.ctl.part_out != nullptr) {
+      const double tot = block_sum_all(sq, shc);
+      if (tid == 0) a.ctl.part_out[vb.x] = tot;
+    }
+  }
+}
+
+template <typename R, int P, bool INV, bool SCALE, bool EPI, bool GROUPED>
+__global__ __launch_bounds__((RegCfg<R, P>::T), (RegCfg<R, P>::WAVES)) void tube_reg_kernel(FastArgs a_, const FastArgs* grp,
+                                                                   const int4* bmap) {
+  if constexpr (!GROUPED) {
+    tube_reg_body<R, P, INV, SCALE, EPI>(a_, hw_block());
+  } else {
+    VBlock vb;
+    const FastArgs g = group_args(grp, bmap, vb);
+    tube_reg_body<R, P, INV, SCALE, EPI>(g, vb);
+  }
+}
+
 int ilog2(int64_t v) {
   int l = 0;
   while ((int64_t)1 << l < v) ++l;
@@ -423,6 +867,45 @@ int tube_fast_max(int dtype) { return dtype == DCTK_F64 ? FastCfg<double>::E : F
 
 bool tube_fast_shape_ok(int dtype, int64_t p) {
   return p >= kFastMinTube && p <= tube_fast_max(dtype) && (p & (p - 1)) == 0;
+}
+
+// Tubes of 128 to 1024 positions (where LDS ends), results of the input's type:
+// tube_reg_body.  A 16-bit result keeps the LDS kernel, whose sums it rounds.
+static bool tube_reg_ok(int in_dtype, int out_dtype, int64_t p) {
+  return in_dtype == out_dtype && p >= 128 && p <= 1024;
+}
+
+template <typename R, int P>
+static hipError_t launch_reg(dctk_ctx ctx, hipStream_t s, FastArgs& a, bool scale, bool epi, int* nblocks_out) {
+  typedef RegCfg<R, P> G;
+  // resident workgroups, each looping over tiles
+  const int64_t blocks = std::min<int64_t>((a.count + G::NB - 1) / G::NB, G::PER_CU * (int64_t)num_cus());
+  if (nblocks_out) *nblocks_out = (int)blocks;
+  a.group = 1;
+  const dim3 g((unsigned)blocks);
+#define DCTK_REG(I, S, E_, GR) \
+  return launch_kernel(ctx, s, tube_reg_kernel<R, P, I, S, E_, false>, tube_reg_kernel<R, P, I, S, E_, GR>, g, G::T, 0, a)
+  if (scale) DCTK_REG(false, true, false, true);
+  if (epi) DCTK_REG(true, false, true, true);
+  if (a.inv) DCTK_REG(true, false, false, false);  // not part of a batch
+  DCTK_REG(false, false, false, false);
+#undef DCTK_REG
+}
+
+static hipError_t launch_reg_p(dctk_ctx ctx, hipStream_t s, int dtype, FastArgs& a, bool scale, bool epi,
+                               int* nblocks_out) {
+#define DCTK_REG_P(R, P) return launch_reg<R, P>(ctx, s, a, scale, epi, nblocks_out)
+  if (dtype == DCTK_F64) {
+    if (a.p == 128) DCTK_REG_P(double, 128);
+    if (a.p == 256) DCTK_REG_P(double, 256);
+    if (a.p == 512) DCTK_REG_P(double, 512);
+    DCTK_REG_P(double, 1024);
+  }
+  if (a.p == 128) DCTK_REG_P(float, 128);
+  if (a.p == 256) DCTK_REG_P(float, 256);
+  if (a.p == 512) DCTK_REG_P(float, 512);
+  DCTK_REG_P(float, 1024);
+#undef DCTK_REG_P
 }
 
 // The arguments of transform `which` of family `tube` on p x count elements
@@ -468,6 +951,7 @@ hipError_t launch_tube_fast(dctk_ctx ctx, hipStream_t s, int tube, int which, in
   a.out = out;
   a.ctl.kind = CTL_PLAIN;
   const dim3 g((unsigned)blocks);
+  if (tube_reg_ok(dtype, dtype, p)) return launch_reg_p(ctx, s, dtype, a, false, false, nullptr);
   const bool pair = a.nb >= 2;
 #define DCTK_FAST_PLAIN(T, I, P) \
   return launch_kernel(ctx, s, tube_fast_kernel<T, T, I, P, false, false, false>, \
@@ -506,6 +990,7 @@ hipError_t launch_tube_fast_ctl(dctk_ctx ctx, hipStream_t s, int tube, int which
   a.xnorm = scale ? xnorm : nullptr;
   a.ctl = ctl;
   const dim3 g((unsigned)blocks);
+  if (tube_reg_ok(in_dtype, out_dtype, p)) return launch_reg_p(ctx, s, in_dtype, a, scale, epi, nblocks_out);
   const bool pair = a.nb >= 2;
 #define DCTK_FAST_CTL(T, TO, I, P, S, E_)                                                         \
   return launch_kernel(ctx, s, tube_fast_kernel<T, TO, I, P, S, E_, false>,                       \
