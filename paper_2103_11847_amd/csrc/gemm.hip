@@ -21,9 +21,6 @@ namespace dctk {
 // batches of at least this many slices are placed per XCD (slice_block)
 constexpr int kSliceXcdMin = 16;
 
-// threads of a 16-bit GEMM workgroup: 512 for 256 x 256 tiles, else 256
-__host__ __device__ constexpr int gemm_threads(int bm, int bn) { return bm * bn >= 65536 ? 512 : 256; }
-
 struct GemmArgs {
   int gx, gy, gz;
   int M, N, K;
@@ -57,13 +54,38 @@ __device__ inline bool slice_block(const GemmArgs& ga, VBlock& vb) {
   return true;
 }
 
-// VEC (16-bit types): operands move as 16-byte vectors of 8 elements along
-// their contiguous dimension (multiples of 8, 16-byte aligned): an operand
-// contiguous in k goes to its LDS rows as one 16-byte store, one contiguous
-// in m (or n) is transposed on the way, as eight 2-byte stores into eight
-// rows at one k.  All loads are issued from clamped addresses and selected.
-template <typename TI, typename TO, int BM, int BN, bool TA, bool TB, bool VEC>
-__device__ __forceinline__ void gemm_kernel_body(const GemmArgs& ga, const VBlock vb, const bool grouped) {
+// Eight 16-bit elements at any address (a 2-byte aligned 16-byte load).
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4_un __attribute__((ext_vector_type(4), aligned(2)));
+template <typename TI>
+__device__ __forceinline__ u32x4 load8(const TI* p) {
+  return *reinterpret_cast<const u32x4_un*>(p);
+}
+// A unit of 8 elements whose load was moved back by n elements to end with its
+// row: elements n .. 7 to the front, 0 behind them (n <= 0: as loaded).
+__device__ __forceinline__ u32x4 drop8(u32x4 v, int n) {
+  if (n <= 0) return v;
+  if (n >= 8) return u32x4{0u, 0u, 0u, 0u};
+  if (n & 4) v = u32x4{v.z, v.w, 0u, 0u};
+  if (n & 2) v = u32x4{v.y, v.z, v.w, 0u};
+  if (n & 1)
+    v = u32x4{__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16),
+              __builtin_amdgcn_alignbit(v.w, v.z, 16), v.w >> 16};
+  return v;
+}
+
+// 16-bit slice GEMM, A~ contiguous in k.  VEC (K >= 8, and N >= 8 for B
+// contiguous in n): operands move as 8-element units along their contiguous
+// dimension, at any alignment and any size: rows beyond an operand are read
+// from its last row, a unit that would cross the end of its row is loaded
+// from the row's last 8 elements and put right when it is staged, where its
+// wait is.  An operand contiguous in k goes to its LDS rows as one 16-byte
+// store, one contiguous in n is transposed on the way, as eight stores into
+// eight rows.  Sizes that were no multiple of 8 took 2-byte loads before:
+// 64 x 637^3 BF16 200 us (640^3: 87), now 97 (85); 31 x 501^3 67 (504^3: 32), now
+// 37 (31); 32 x 302^3, two products a slice, 51 (304^3: 25), now 27 (26).
+template <typename TI, typename TO, int BM, int BN, bool TB, bool VEC>
+__device__ __forceinline__ void gemm_kernel_body(const GemmArgs& ga, const VBlock vb) {
   const int M = ga.M, N = ga.N, K = ga.K;
   const TI* __restrict__ A = (const TI*)ga.A;
   const TI* __restrict__ B = (const TI*)ga.B;
@@ -76,15 +98,11 @@ __device__ __forceinline__ void gemm_kernel_body(const GemmArgs& ga, const VBloc
   constexpr int KSTEP = MF::KSTEP;
   // 256-row tiles: 32-wide contraction chunks (the two operand tiles of a
   // 256 x 128 chunk are 30 KB of LDS, so two workgroups share a CU)
-  constexpr int BK = (KSTEP == 4) ? 16 : (BM >= 256 ? 32 : 64);
-  constexpr int PAD = (sizeof(TI) == 2) ? 8 : (sizeof(TI) == 4 ? 4 : 2);  // 16 bytes
-  constexpr int LDS_LD = BK + PAD;
-  constexpr int NT = gemm_threads(BM, BN), WGM = 2, WGN = NT / 128;   // threads, wave grid
-  constexpr int A_PER = (BM * BK + NT - 1) / NT;  // elements of the A tile per thread
-  constexpr int B_PER = (BN * BK + NT - 1) / NT;
+  constexpr int BK = BM >= 256 ? 32 : 64;
+  constexpr int LDS_LD = BK + 8;   // 16-byte pad
+  constexpr int NT = 256, WGM = 2, WGN = NT / 128;   // threads, wave grid
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int FM = WM / 16, FN = WN / 16;
-  static_assert(A_PER >= 1 && B_PER >= 1, "tile too small");
 
   if (!gate_open(g)) return;
 
@@ -103,34 +121,27 @@ __device__ __forceinline__ void gemm_kernel_body(const GemmArgs& ga, const VBloc
   const int wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
 
-  // element (r, kk) of the A tile (r < BM, kk < BK) handled by this thread, slot u
-  auto a_coord = [&](int u, int& r, int& kk) {
-    int idx = tid + u * NT;
-    if (!TA) { r = idx / BK; kk = idx % BK; }   // contiguous along k
-    else     { kk = idx / BM; r = idx % BM; }   // contiguous along m
-  };
+  // scalar staging
+  constexpr int A_PER = VEC ? 1 : BM * BK / NT, B_PER = VEC ? 1 : BN * BK / NT;  // elements per thread
+  TI ra[A_PER], rb[B_PER];
   auto b_coord = [&](int u, int& c, int& kk) {
-    int idx = tid + u * NT;
+    const int idx = tid + u * NT;
     if (!TB) { kk = idx / BN; c = idx % BN; }   // contiguous along n
     else     { c = idx / BK; kk = idx % BK; }   // contiguous along k
   };
-
-  TI ra[A_PER], rb[B_PER];
   auto load_tiles = [&](int k0) {
 #pragma unroll
     for (int u = 0; u < A_PER; ++u) {
-      int r, kk;
-      a_coord(u, r, kk);
-      int gm = m0 + r, gk = k0 + kk;
+      const int idx = tid + u * NT, gm = m0 + idx / BK, gk = k0 + idx % BK;
       TI v = (TI)0;
-      if (gm < M && gk < K) v = TA ? A[(int64_t)gk * lda + gm] : A[(int64_t)gm * lda + gk];
+      if (gm < M && gk < K) v = A[(int64_t)gm * lda + gk];
       ra[u] = v;
     }
 #pragma unroll
     for (int u = 0; u < B_PER; ++u) {
       int c, kk;
       b_coord(u, c, kk);
-      int gn = n0 + c, gk = k0 + kk;
+      const int gn = n0 + c, gk = k0 + kk;
       TI v = (TI)0;
       if (gn < N && gk < K) v = TB ? B[(int64_t)gn * ldb + gk] : B[(int64_t)gk * ldb + gn];
       rb[u] = v;
@@ -139,9 +150,8 @@ __device__ __forceinline__ void gemm_kernel_body(const GemmArgs& ga, const VBloc
   auto store_tiles = [&]() {
 #pragma unroll
     for (int u = 0; u < A_PER; ++u) {
-      int r, kk;
-      a_coord(u, r, kk);
-      As[r * LDS_LD + kk] = ra[u];
+      const int idx = tid + u * NT;
+      As[idx / BK * LDS_LD + idx % BK] = ra[u];
     }
 #pragma unroll
     for (int u = 0; u < B_PER; ++u) {
@@ -151,85 +161,79 @@ __device__ __forceinline__ void gemm_kernel_body(const GemmArgs& ga, const VBloc
     }
   };
 
-  // vector staging (VEC).  An operand contiguous in k moves in units of 8 k
-  // of one row (one 16-byte load and LDS store); an operand contiguous in its
-  // rows moves in units of 8 rows x KU k (KU 16-byte loads), transposed in
-  // registers into 8 rows of KU consecutive k (eight LDS stores of KU
-  // elements).
-  constexpr int KU = 8;
+  // vector staging: units of 8 k of a row, or of 8 rows x 8 k transposed in registers
   struct H8 { TI v[8]; };
-  struct HK { TI v[KU]; };
-  typedef typename std::conditional<KU == 8, uint4, uint2>::type kvec_t;
-  constexpr int A_NK = TA ? BM * BK / (8 * KU) : BM * BK / 8;   // units of the A tile
-  constexpr int B_NK = TB ? BN * BK / 8 : BN * BK / (8 * KU);
-  constexpr int A_UV = (A_NK + NT - 1) / NT, B_UV = (B_NK + NT - 1) / NT;
-  constexpr int A_L = TA ? KU : 1, B_L = TB ? 1 : KU;       // 16-byte loads per unit
-  uint4 va[A_UV][A_L], vbv[B_UV][B_L];
+  constexpr int A_NK = BM * BK / 8;                          // units of the A tile
+  constexpr int B_NK = TB ? BN * BK / 8 : BN * BK / 64;
+  constexpr int A_UV = VEC ? (A_NK + NT - 1) / NT : 1, B_UV = VEC ? (B_NK + NT - 1) / NT : 1;
+  constexpr int B_L = TB ? 1 : 8;                            // loads per unit
+  u32x4 va[A_UV], vbv[B_UV][B_L];
   // unit u of an operand tile of R rows: its first (row, k)
   auto unit = [&](int u, int R, bool kcontig, int& r, int& kk) {
     const int idx = tid + u * NT;
     if (kcontig) { r = idx / (BK / 8); kk = (idx % (BK / 8)) * 8; }
-    else         { kk = (idx / (R / 8)) * KU; r = (idx % (R / 8)) * 8; }
+    else         { kk = (idx / (R / 8)) * 8; r = (idx % (R / 8)) * 8; }
   };
+  auto at_most = [](int v, int lim) { return v < lim ? v : lim; };
   auto load_vec = [&](int k0) {
 #pragma unroll
     for (int u = 0; u < A_UV; ++u) {
       int r, kk;
-      unit(u, BM, !TA, r, kk);
-      const bool ok = A_NK % NT == 0 || tid + u * NT < A_NK;
-#pragma unroll
-      for (int l = 0; l < A_L; ++l) {
-        const int gm = m0 + r, gk = k0 + kk + l;
-        const bool in = ok && gm < M && gk < K;
-        const int64_t off = in ? (TA ? (int64_t)gk * lda + gm : (int64_t)gm * lda + gk) : 0;
-        const uint4 v = *reinterpret_cast<const uint4*>(A + off);
-        va[u][l] = in ? v : make_uint4(0u, 0u, 0u, 0u);
-      }
+      unit(u, BM, true, r, kk);
+      va[u] = load8(A + (int64_t)at_most(m0 + r, M - 1) * lda + at_most(k0 + kk, K - 8));
     }
 #pragma unroll
     for (int u = 0; u < B_UV; ++u) {
       int c, kk;
       unit(u, BN, TB, c, kk);
-      const bool ok = B_NK % NT == 0 || tid + u * NT < B_NK;
+      if (B_NK % NT != 0 && tid + u * NT >= B_NK) continue;
 #pragma unroll
-      for (int l = 0; l < B_L; ++l) {
-        const int gn = n0 + c, gk = k0 + kk + l;
-        const bool in = ok && gn < N && gk < K;
-        const int64_t off = in ? (TB ? (int64_t)gn * ldb + gk : (int64_t)gk * ldb + gn) : 0;
-        const uint4 v = *reinterpret_cast<const uint4*>(B + off);
-        vbv[u][l] = in ? v : make_uint4(0u, 0u, 0u, 0u);
-      }
+      for (int l = 0; l < B_L; ++l)
+        vbv[u][l] = load8(B + (TB ? (int64_t)at_most(n0 + c, N - 1) * ldb + at_most(k0 + kk, K - 8)
+                                  : (int64_t)at_most(k0 + kk + l, K - 1) * ldb + at_most(n0 + c, N - 8)));
     }
   };
-  // 8 rows x KU k held as KU 16-byte rows along the operand's rows -> LDS
-  auto put_t = [&](TI* S, int r, int kk, const uint4 (&q)[KU]) {
-    H8 h[KU];
-#pragma unroll
-    for (int l = 0; l < KU; ++l) h[l] = __builtin_bit_cast(H8, q[l]);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      HK w;
-#pragma unroll
-      for (int l = 0; l < KU; ++l) w.v[l] = h[l].v[j];
-      *reinterpret_cast<kvec_t*>(&S[(r + j) * LDS_LD + kk]) = __builtin_bit_cast(kvec_t, w);
-    }
-  };
-  auto store_vec = [&]() {
+  auto store_vec = [&](int k0) {
+    const bool kend = k0 + BK > K, nend = n0 + BN > N;   // uniform
 #pragma unroll
     for (int u = 0; u < A_UV; ++u) {
       if (A_NK % NT != 0 && tid + u * NT >= A_NK) continue;
       int r, kk;
-      unit(u, BM, !TA, r, kk);
-      if constexpr (!TA) *reinterpret_cast<uint4*>(&As[r * LDS_LD + kk]) = va[u][0];
-      else put_t(As, r, kk, va[u]);
+      unit(u, BM, true, r, kk);
+      u32x4 v = va[u];
+      if (kend) v = drop8(v, k0 + kk - (K - 8));
+      *reinterpret_cast<u32x4*>(&As[r * LDS_LD + kk]) = v;
     }
 #pragma unroll
     for (int u = 0; u < B_UV; ++u) {
       if (B_NK % NT != 0 && tid + u * NT >= B_NK) continue;
       int c, kk;
       unit(u, BN, TB, c, kk);
-      if constexpr (TB) *reinterpret_cast<uint4*>(&Bs[c * LDS_LD + kk]) = vbv[u][0];
-      else put_t(Bs, c, kk, vbv[u]);
+      if constexpr (TB) {
+        u32x4 v = vbv[u][0];
+        if (kend) v = drop8(v, k0 + kk - (K - 8));
+        *reinterpret_cast<u32x4*>(&Bs[c * LDS_LD + kk]) = v;
+      } else {
+        if (nend) {
+#pragma unroll
+          for (int l = 0; l < 8; ++l) vbv[u][l] = drop8(vbv[u][l], n0 + c - (N - 8));
+        }
+        if (kend) {
+#pragma unroll
+          for (int l = 0; l < 8; ++l)
+            if (k0 + kk + l >= K) vbv[u][l] = u32x4{0u, 0u, 0u, 0u};
+        }
+        H8 h[8];
+#pragma unroll
+        for (int l = 0; l < 8; ++l) h[l] = __builtin_bit_cast(H8, vbv[u][l]);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          H8 w;
+#pragma unroll
+          for (int l = 0; l < 8; ++l) w.v[l] = h[l].v[j];
+          *reinterpret_cast<u32x4*>(&Bs[(c + j) * LDS_LD + kk]) = __builtin_bit_cast(u32x4, w);
+        }
+      }
     }
   };
 
@@ -248,7 +252,7 @@ __device__ __forceinline__ void gemm_kernel_body(const GemmArgs& ga, const VBloc
   else load_tiles(0);
   for (int k0 = 0; k0 < K; k0 += BK) {
     __syncthreads();
-    if constexpr (VEC) store_vec();
+    if constexpr (VEC) store_vec(k0);
     else store_tiles();
     __syncthreads();
     // prefetch the next chunk into registers
@@ -288,17 +292,169 @@ __device__ __forceinline__ void gemm_kernel_body(const GemmArgs& ga, const VBloc
     }
 }
 
-template <typename TI, typename TO, int BM, int BN, bool TA, bool TB, bool VEC, bool GROUPED>
-__global__ __launch_bounds__(gemm_threads(BM, BN)) void gemm_kernel(GemmArgs ga_, const GemmArgs* grp, const int4* bmap) {
+template <typename TI, typename TO, int BM, int BN, bool TB, bool VEC, bool GROUPED>
+__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs ga_, const GemmArgs* grp, const int4* bmap) {
   if constexpr (!GROUPED) {
     VBlock vb = hw_block();
     if (!slice_block(ga_, vb)) return;
-    gemm_kernel_body<TI, TO, BM, BN, TA, TB, VEC>(ga_, vb, false);
+    gemm_kernel_body<TI, TO, BM, BN, TB, VEC>(ga_, vb);
   } else {
     VBlock vb;
     const GemmArgs g = group_args(grp, bmap, vb);
     if (!slice_block(g, vb)) return;   // the instance's grid may be padded
-    gemm_kernel_body<TI, TO, BM, BN, TA, TB, VEC>(g, vb, true);
+    gemm_kernel_body<TI, TO, BM, BN, TB, VEC>(g, vb);
+  }
+}
+
+// The same with 64 x 64 or 32 x 32 tiles: the slices of video and of small
+// cubes, a few chunks of K each, where the time is that of the loads' round
+// trips.  So the next kRing chunks (64 k) of both operands are in flight in
+// registers, and one barrier a chunk separates the two LDS buffers.  B
+// contiguous in n moves in units of 2 k x 8 n, paired on the way into 8 LDS
+// rows.  LDS rows are 8 blocks of 16 bytes, block b of row r at
+// b ^ (r ^ r / 8) % 8: neither the stores of 8 rows 8 apart nor the operand
+// reads of 8 neighbouring rows meet in a bank.  Two FP16 products
+// a slice, with one chunk in flight and now: 32 x 256^3 18.7 -> 17.8 us, 20 x
+// 320^3 31.8 -> 28.3.  The sums are those of gemm_kernel, bit for bit.
+template <typename TI, typename TO, int BT, bool TB>
+__device__ __forceinline__ void gemm_ring_body(const GemmArgs& ga, const VBlock vb) {
+  typedef Mfma<TI> MF;
+  constexpr int BK = 64, kRing = 4, U = BT / 32, F = BT / 32;   // row units of a thread; 16 x 16 blocks of a wave: F x F
+  if (!gate_open(ga.g)) return;
+  __shared__ u32x4 S[2][2][BT * 8];   // buffer, operand
+  const int M = ga.M, N = ga.N, K = ga.K;
+  const int64_t lda = ga.lda, ldb = ga.ldb;
+  const int m0 = vb.y * BT, n0 = vb.x * BT;
+  const TI* A = (const TI*)ga.A + (int64_t)vb.z * ga.sA;
+  const TI* B = (const TI*)ga.B + (int64_t)vb.z * ga.sB;
+  TO* __restrict__ C = (TO*)ga.C + (int64_t)vb.z * ga.sC;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1, lr = lane & 15, lg = lane >> 4;
+  auto slot = [](int r, int b) { return r * 8 + (b ^ ((r ^ (r >> 3)) & 7)); };
+  auto at_most = [](int v, int lim) { return v < lim ? v : lim; };
+  // operands contiguous in k: rows ur + 32 u, k 8 ub; B contiguous in n: k 2 kr and 2 kr + 1, n 8 nb
+  const int ur = tid >> 3, ub = tid & 7, kr = tid / (BT / 8), nb = tid % (BT / 8);
+  const bool pairs = BT == 64 || kr < 32;
+  const TI *pa[U], *pb[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    pa[u] = A + (int64_t)at_most(m0 + ur + 32 * u, M - 1) * lda;
+    pb[u] = TB ? B + (int64_t)at_most(n0 + ur + 32 * u, N - 1) * ldb : B + at_most(n0 + 8 * nb, N - 8);
+  }
+  constexpr int BU = TB ? U : 2;
+  u32x4 ra[kRing][U], rb[kRing][BU];
+  auto load = [&](int k0, u32x4 (&va)[U], u32x4 (&vb_)[BU]) {
+    const int k = at_most(k0 + 8 * ub, K - 8);
+#pragma unroll
+    for (int u = 0; u < U; ++u) va[u] = load8(pa[u] + k);
+    if constexpr (TB) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) vb_[u] = load8(pb[u] + k);
+    } else if (pairs) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) vb_[u] = load8(pb[0] + (int64_t)at_most(k0 + 2 * kr + u, K - 1) * ldb);
+    }
+  };
+  auto store = [&](int k0, int b, const u32x4 (&va)[U], const u32x4 (&vb_)[BU]) {
+    const bool kend = k0 + BK > K;   // uniform
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      u32x4 v = va[u];
+      if (kend) v = drop8(v, k0 + 8 * ub - (K - 8));
+      S[b][0][slot(ur + 32 * u, ub)] = v;
+    }
+    if constexpr (TB) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        u32x4 v = vb_[u];
+        if (kend) v = drop8(v, k0 + 8 * ub - (K - 8));
+        S[b][1][slot(ur + 32 * u, ub)] = v;
+      }
+    } else if (pairs) {
+      u32x4 x = vb_[0], y = vb_[1];
+      if (n0 + BT > N) {
+        x = drop8(x, n0 + 8 * nb - (N - 8));
+        y = drop8(y, n0 + 8 * nb - (N - 8));
+      }
+      if (kend) {
+        x = k0 + 2 * kr < K ? x : u32x4{0u, 0u, 0u, 0u};
+        y = k0 + 2 * kr + 1 < K ? y : u32x4{0u, 0u, 0u, 0u};
+      }
+      unsigned* w = reinterpret_cast<unsigned*>(&S[b][1][0]);
+      const unsigned xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const unsigned a = xs[j / 2], c = ys[j / 2];
+        w[slot(nb * 8 + j, kr >> 2) * 4 + (kr & 3)] = j & 1 ? a >> 16 | (c & 0xffff0000u) : (a & 0xffffu) | c << 16;
+      }
+    }
+  };
+  typename MF::frag_t acc[F][F];
+#pragma unroll
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int j = 0; j < F; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
+  const int nc = (K + BK - 1) / BK;
+#pragma unroll
+  for (int d = 0; d < kRing; ++d)
+    if (d < nc) load(d * BK, ra[d], rb[d]);
+  store(0, 0, ra[0], rb[0]);
+  if (kRing < nc) load(kRing * BK, ra[0], rb[0]);
+  __syncthreads();
+  for (int c0 = 0; c0 < nc; c0 += kRing) {
+#pragma unroll
+    for (int d = 0; d < kRing; ++d) {
+      const int c = c0 + d;
+      if (c >= nc) break;
+      const int q = (d + 1) % kRing;
+      if (c + 1 < nc) {
+        store((c + 1) * BK, (c + 1) & 1, ra[q], rb[q]);
+        if (c + 1 + kRing < nc) load((c + 1 + kRing) * BK, ra[q], rb[q]);
+      }
+      const u32x4 *SA = S[c & 1][0], *SB = S[c & 1][1];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const TI *ap[F], *bp[F];
+#pragma unroll
+        for (int i = 0; i < F; ++i) {
+          ap[i] = reinterpret_cast<const TI*>(&SA[slot((wm * F + i) * 16 + lr, ks * 4 + lg)]);
+          bp[i] = reinterpret_cast<const TI*>(&SB[slot((wn * F + i) * 16 + lr, ks * 4 + lg)]);
+        }
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+          for (int j = 0; j < F; ++j) acc[i][j] = MF::mac(ap[i], bp[j], acc[i][j]);
+      }
+      __syncthreads();
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int j = 0; j < F; ++j) {
+      const int col = n0 + (wn * F + j) * 16 + lr;
+      if (col >= N) continue;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = m0 + (wm * F + i) * 16 + lg * 4 + r;
+        if (row < M) C[(int64_t)row * ga.ldc + col] = out_cvt<TO, float>(acc[i][j][r]);
+      }
+    }
+}
+
+template <typename TI, typename TO, int BT, bool TB, bool GROUPED>
+__global__ __launch_bounds__(256, 4) void gemm_ring_kernel(GemmArgs ga_, const GemmArgs* grp, const int4* bmap) {
+  if constexpr (!GROUPED) {
+    VBlock vb = hw_block();
+    if (!slice_block(ga_, vb)) return;
+    gemm_ring_body<TI, TO, BT, TB>(ga_, vb);
+  } else {
+    VBlock vb;
+    const GemmArgs g = group_args(grp, bmap, vb);
+    if (!slice_block(g, vb)) return;
+    gemm_ring_body<TI, TO, BT, TB>(g, vb);
   }
 }
 
@@ -795,14 +951,14 @@ static hipError_t launch_gemm_vec(dctk_ctx ctx, hipStream_t s, int M, int N, int
   return launch_gemm_mn<T, 32, 32, BK>(ctx, s, ga, ta, tb, vec, batch);
 }
 
-template <typename TI, typename TO, int BM, int BN>
-static hipError_t launch_gemm_tile(dctk_ctx ctx, hipStream_t s, int M, int N, int K, const void* A, int64_t lda,
-                                   int64_t sA, int ta, const void* B, int64_t ldb, int64_t sB, int tb,
-                                   void* C, int64_t ldc, int64_t sC, int batch, Gate g) {
+template <typename TI, typename TO>
+static hipError_t launch_gemm_t(dctk_ctx ctx, hipStream_t s, int M, int N, int K, const void* A, int64_t lda, int64_t sA,
+                                int ta, const void* B, int64_t ldb, int64_t sB, int tb, void* C, int64_t ldc,
+                                int64_t sC, int batch, Gate g, int num_cus, int tile) {
+  if (ta) return hipErrorInvalidValue;   // 16-bit operators keep A~ transposed
   GemmArgs ga{};
   ga.nbatch = batch >= kSliceXcdMin ? batch : 0;
   const int gz = ga.nbatch > 0 ? (batch + 7) / 8 * 8 : batch;
-  dim3 grid((unsigned)((N + BN - 1) / BN), (unsigned)((M + BM - 1) / BM), (unsigned)gz);
   ga.M = M;
   ga.N = N;
   ga.K = K;
@@ -816,26 +972,16 @@ static hipError_t launch_gemm_tile(dctk_ctx ctx, hipStream_t s, int M, int N, in
   ga.ldc = ldc;
   ga.sC = sC;
   ga.g = g;
-  // 16-byte vectors: 8 elements along each operand's contiguous dimension
-  const bool va = (ta ? M % 8 == 0 : K % 8 == 0) && lda % 8 == 0 && sA % 8 == 0 && ((uintptr_t)A % 16) == 0;
-  const bool vb = (tb ? K % 8 == 0 : N % 8 == 0) && ldb % 8 == 0 && sB % 8 == 0 && ((uintptr_t)B % 16) == 0;
-  const bool vec = sizeof(TI) == 2 && va && vb;
-#define DCTK_GEMM_LAUNCH(TA_, TB_) \
-  do { \
-    if (vec) return launch_kernel(ctx, s, gemm_kernel<TI, TO, BM, BN, TA_, TB_, true, false>, gemm_kernel<TI, TO, BM, BN, TA_, TB_, true, true>, grid, gemm_threads(BM, BN), 0, ga); \
-    return launch_kernel(ctx, s, gemm_kernel<TI, TO, BM, BN, TA_, TB_, false, false>, gemm_kernel<TI, TO, BM, BN, TA_, TB_, false, true>, grid, gemm_threads(BM, BN), 0, ga); \
+  auto grid = [&](int bm, int bn) { return dim3((unsigned)((N + bn - 1) / bn), (unsigned)((M + bm - 1) / bm), (unsigned)gz); };
+#define DCTK_GEMM16(KERNEL, BM, BN, ...)                                                                \
+  do {                                                                                                  \
+    if (tb) return launch_kernel(ctx, s, KERNEL(true, false, __VA_ARGS__), KERNEL(true, true, __VA_ARGS__), grid(BM, BN), 256, 0, ga); \
+    return launch_kernel(ctx, s, KERNEL(false, false, __VA_ARGS__), KERNEL(false, true, __VA_ARGS__), grid(BM, BN), 256, 0, ga);       \
   } while (0)
-  if (!ta && !tb) DCTK_GEMM_LAUNCH(false, false);
-  if (ta && !tb) DCTK_GEMM_LAUNCH(true, false);
-  if (!ta && tb) DCTK_GEMM_LAUNCH(false, true);
-  DCTK_GEMM_LAUNCH(true, true);
-#undef DCTK_GEMM_LAUNCH
-}
-
-template <typename TI, typename TO>
-static hipError_t launch_gemm_t(dctk_ctx ctx, hipStream_t s, int M, int N, int K, const void* A, int64_t lda, int64_t sA,
-                                int ta, const void* B, int64_t ldb, int64_t sB, int tb, void* C, int64_t ldc,
-                                int64_t sC, int batch, Gate g, int num_cus, int tile) {
+#define DCTK_TILED(TB_, GR, BM, BN, VEC) gemm_kernel<TI, TO, BM, BN, TB_, VEC, GR>
+#define DCTK_RING(TB_, GR, BT) gemm_ring_kernel<TI, TO, BT, TB_, GR>
+  // shorter than a unit: scalar loads (32 x 32 tiles: the result is a few columns, or the sums short)
+  if (K < 8 || (!tb && N < 8)) DCTK_GEMM16(DCTK_TILED, 32, 32, 32, 32, false);
   // 128 x 128 tiles while they give every CU two, then 64 x 64 when they
   // fill the chip, 32 x 32 otherwise.
   const int64_t tiles256 = (int64_t)((M + 255) / 256) * ((N + 255) / 256) * batch;
@@ -845,12 +991,13 @@ static hipError_t launch_gemm_t(dctk_ctx ctx, hipStream_t s, int M, int N, int K
   // byte staged serves 4/3 the flops of a 128 x 128 tile, and two workgroups
   // of 4 waves per CU hide more latency than one of 8 with 256 x 256 tiles)
   if (tile == 256 || (tile == 0 && M >= 256 && N >= 256 && tiles256 >= (int64_t)num_cus))
-    return launch_gemm_tile<TI, TO, 256, 128>(ctx, s, M, N, K, A, lda, sA, ta, B, ldb, sB, tb, C, ldc, sC, batch, g);
-  if (tile == 128 || (tile == 0 && tiles128 >= 2 * (int64_t)num_cus))
-    return launch_gemm_tile<TI, TO, 128, 128>(ctx, s, M, N, K, A, lda, sA, ta, B, ldb, sB, tb, C, ldc, sC, batch, g);
-  if (tile == 64 || (tile == 0 && tiles64 >= 2 * (int64_t)num_cus))
-    return launch_gemm_tile<TI, TO, 64, 64>(ctx, s, M, N, K, A, lda, sA, ta, B, ldb, sB, tb, C, ldc, sC, batch, g);
-  return launch_gemm_tile<TI, TO, 32, 32>(ctx, s, M, N, K, A, lda, sA, ta, B, ldb, sB, tb, C, ldc, sC, batch, g);
+    DCTK_GEMM16(DCTK_TILED, 256, 128, 256, 128, true);
+  if (tile == 128 || (tile == 0 && tiles128 >= 2 * (int64_t)num_cus)) DCTK_GEMM16(DCTK_TILED, 128, 128, 128, 128, true);
+  if (tile == 64 || (tile == 0 && tiles64 >= 2 * (int64_t)num_cus)) DCTK_GEMM16(DCTK_RING, 64, 64, 64);
+  DCTK_GEMM16(DCTK_RING, 32, 32, 32);
+#undef DCTK_RING
+#undef DCTK_TILED
+#undef DCTK_GEMM16
 }
 
 static int g_num_cus = 256;
