@@ -71,37 +71,76 @@ int build_tube_matrix(int tube, int which, int64_t p, double* out) {
 }
 
 // ---- device: the streaming transform ----------------------------------------
-template <typename T> struct Vec4Load;
-template <> struct Vec4Load<float> {
-  __device__ static void load(const float* p, float* v) {
-    float4 q = *reinterpret_cast<const float4*>(p);
-    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+// Four neighbouring positions of a slice in memory: one 16-byte (32, 8) access
+// that needs no more than the element's own alignment, so slices of any size
+// and buffers at any address move in vectors.
+typedef float f32x4_un __attribute__((ext_vector_type(4), aligned(4)));
+typedef double f64x2_un __attribute__((ext_vector_type(2), aligned(8)));
+typedef unsigned int u32x2_un __attribute__((ext_vector_type(2), aligned(2)));
+typedef _Float16 f16x4_un __attribute__((ext_vector_type(4), aligned(2)));
+__device__ inline void load4(const float* p, float (&v)[4]) {
+  const f32x4_un q = *reinterpret_cast<const f32x4_un*>(p);
+  v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+}
+__device__ inline void load4(const double* p, double (&v)[4]) {
+  const f64x2_un a = *reinterpret_cast<const f64x2_un*>(p), b = *reinterpret_cast<const f64x2_un*>(p + 2);
+  v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+}
+__device__ inline void store4(float* p, const float (&v)[4]) {
+  *reinterpret_cast<f32x4_un*>(p) = f32x4_un{v[0], v[1], v[2], v[3]};
+}
+__device__ inline void store4(double* p, const double (&v)[4]) {
+  *reinterpret_cast<f64x2_un*>(p) = f64x2_un{v[0], v[1]};
+  *reinterpret_cast<f64x2_un*>(p + 2) = f64x2_un{v[2], v[3]};
+}
+__device__ inline void store4(bf16_t* p, const float (&v)[4]) {
+  const unsigned lo = (unsigned)float_to_bf16(v[0]) | ((unsigned)float_to_bf16(v[1]) << 16);
+  const unsigned hi = (unsigned)float_to_bf16(v[2]) | ((unsigned)float_to_bf16(v[3]) << 16);
+  *reinterpret_cast<u32x2_un*>(p) = u32x2_un{lo, hi};
+}
+__device__ inline void store4(f16_t* p, const float (&v)[4]) {
+  *reinterpret_cast<f16x4_un*>(p) = f16x4_un{(f16_t)v[0], (f16_t)v[1], (f16_t)v[2], (f16_t)v[3]};
+}
+// positions e .. e + 3 of a slice of `count`, or (inside) four that all lie in it
+template <typename T, typename V>
+__device__ inline void store_row(T* p, int64_t e, int64_t count, const V (&v)[4], bool inside = false) {
+  if (inside || e + 4 <= count) {
+    store4(p + e, v);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (e + i < count) p[e + i] = cvt<T, V>(v[i]);
   }
-};
-template <> struct Vec4Load<double> {
-  __device__ static void load(const double* p, double* v) {
-    double2 a = *reinterpret_cast<const double2*>(p);
-    double2 b = *reinterpret_cast<const double2*>(p + 2);
-    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+}
+// Four values loaded n positions early, to end with their slice: entries n .. 3
+// to the front, 0 behind them (n <= 0: as loaded).
+template <typename T>
+__device__ inline void drop4(T (&v)[4], int64_t n) {
+  if (n <= 0) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    T r = (T)0;
+#pragma unroll
+    for (int j = i + 1; j < 4; ++j) r = n == j - i ? v[j] : r;
+    v[i] = r;
   }
-};
-
-template <typename T> struct Vec4Store {
-  __device__ static void store(T* p, const T* v) {
-    for (int i = 0; i < 4; ++i) p[i] = v[i];
-  }
-};
-template <> struct Vec4Store<float> {
-  __device__ static void store(float* p, const float* v) {
-    *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-  }
-};
-template <> struct Vec4Store<double> {
-  __device__ static void store(double* p, const double* v) {
-    *reinterpret_cast<double2*>(p) = make_double2(v[0], v[1]);
-    *reinterpret_cast<double2*>(p + 2) = make_double2(v[2], v[3]);
-  }
-};
+}
+// four values in LDS, 16-byte aligned
+__device__ inline void lds_load4(const float* p, float (&v)[4]) {
+  const float4 q = *reinterpret_cast<const float4*>(p);
+  v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+}
+__device__ inline void lds_load4(const double* p, double (&v)[4]) {
+  const double2 a = *reinterpret_cast<const double2*>(p), b = *reinterpret_cast<const double2*>(p + 2);
+  v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+}
+__device__ inline void lds_store4(float* p, const float (&v)[4]) {
+  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ inline void lds_store4(double* p, const double (&v)[4]) {
+  *reinterpret_cast<double2*>(p) = make_double2(v[0], v[1]);
+  *reinterpret_cast<double2*>(p + 2) = make_double2(v[2], v[3]);
+}
 
 // TIN: float or double; TOUT: float, double, bf16_t or f16_t; TC: compute type.
 // SCALE: apply the control block's input scale (and write xnorm); EPI: apply
@@ -118,7 +157,7 @@ struct TubeArgs {
   Ctl ctl;
 };
 
-template <typename TIN, typename TOUT, typename TC, int KB, bool VEC, bool SCALE, bool EPI>
+template <typename TIN, typename TOUT, typename TC, int KB, bool SCALE, bool EPI>
 __device__ __forceinline__ void tube_kernel_body(const TubeArgs& ta, const VBlock vb, const bool grouped) {
   __shared__ double sh[kShCtl];
   const int p = ta.p;
@@ -143,44 +182,36 @@ __device__ __forceinline__ void tube_kernel_body(const TubeArgs& ta, const VBloc
   // all p tubes of a 4-position group at once: every input (and src) load
   // of the group is issued before the first use, from clamped addresses
   const bool use_src = EPI && src != nullptr && b != (TC)0;
-  const TOUT* srcl = use_src ? src : out;
-  for (int64_t e0 = ((int64_t)vb.x * blockDim.x + threadIdx.x) * 4; e0 < count; e0 += stride) {
-    const int nv = (count - e0) < 4 ? (int)(count - e0) : 4;
-    TIN xv[KB][4];
-    if (VEC && nv == 4) {
+  // positions e0 .. e0 + 3; tail_c: fewer of them lie in the slice
+  auto do_group = [&](int64_t e0, auto tail_c) {
+    constexpr bool tail = decltype(tail_c)::value;
+    const int nv = tail ? (int)(count - e0) : 4;
+    // rows of `q` (p x count) into v, zeros outside
+    auto rows = [&](const auto* q, auto (&v)[KB][4]) {
 #pragma unroll
       for (int t = 0; t < KB; ++t) {
-        Vec4Load<TIN>::load(in + (int64_t)(t < p ? t : 0) * count + e0, xv[t]);
-        if (t >= p) {
+        const auto* r = q + (int64_t)(t < p ? t : 0) * count + e0;
+        if constexpr (!tail) {
+          load4(r, v[t]);
+        } else {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) xv[t][v] = (TIN)0;
+          for (int i = 0; i < 4; ++i) v[t][i] = r[i < nv ? i : 0];
         }
       }
-    } else {
-#pragma unroll
-      for (int t = 0; t < KB; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const bool ok = t < p && v < nv;
-          const TIN x = in[ok ? (int64_t)t * count + e0 + v : 0];
-          xv[t][v] = ok ? x : (TIN)0;
-        }
-    }
+    };
+    TIN xv[KB][4];
+    rows(in, xv);
     TC sv[KB][4];
-#pragma unroll
-    for (int k = 0; k < KB; ++k)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) sv[k][v] = (TC)0;
-    if (use_src) {
-#pragma unroll
-      for (int k = 0; k < KB; ++k)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const bool ok = k < p && v < nv;
-          const TOUT x = srcl[ok ? (int64_t)k * count + e0 + v : 0];
-          sv[k][v] = ok ? (TC)x : (TC)0;
-        }
+    if constexpr (EPI) {
+      if (use_src) rows(src, sv);
     }
+#pragma unroll
+    for (int t = 0; t < KB; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if (t >= p || (tail && v >= nv)) xv[t][v] = (TIN)0;
+        if (!EPI || !use_src || t >= p || (tail && v >= nv)) sv[t][v] = (TC)0;
+      }
     if (SCALE) {
 #pragma unroll
       for (int t = 0; t < KB; ++t)
@@ -188,13 +219,8 @@ __device__ __forceinline__ void tube_kernel_body(const TubeArgs& ta, const VBloc
         for (int v = 0; v < 4; ++v) xv[t][v] = (TIN)(sc * (TC)xv[t][v]);
       if (xnorm != nullptr) {
 #pragma unroll
-        for (int t = 0; t < KB; ++t) {
-          if (t < p) {
-            TIN* xp = xnorm + (int64_t)t * count + e0;
-            if (VEC && nv == 4) Vec4Store<TIN>::store(xp, xv[t]);
-            else for (int v = 0; v < nv; ++v) xp[v] = xv[t][v];
-          }
-        }
+        for (int t = 0; t < KB; ++t)
+          if (t < p) store_row(xnorm + (int64_t)t * count, e0, count, xv[t], !tail);
       }
     }
 #pragma unroll
@@ -207,21 +233,20 @@ __device__ __forceinline__ void tube_kernel_body(const TubeArgs& ta, const VBloc
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[v] += gk * (TC)xv[t][v];
       }
-      TOUT ov[4];
+      TC ov[4];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         TC r = a * acc[v];
         if (EPI) r += b * sv[k][v];
-        ov[v] = cvt<TOUT, TC>(r);
-        if (EPI && v < nv) {
-          const double rv = (double)r;
-          sq += rv * rv;
-        }
+        ov[v] = r;
+        if (EPI && v < nv) sq += (double)r * (double)r;
       }
-      TOUT* op = out + (int64_t)k * count + e0;
-      if (VEC && nv == 4) Vec4Store<TOUT>::store(op, ov);
-      else for (int v = 0; v < nv; ++v) op[v] = ov[v];
+      store_row(out + (int64_t)k * count, e0, count, ov, !tail);
     }
+  };
+  for (int64_t e0 = ((int64_t)vb.x * blockDim.x + threadIdx.x) * 4; e0 < count; e0 += stride) {
+    if (e0 + 4 <= count) do_group(e0, std::false_type{});
+    else do_group(e0, std::true_type{});
   }
   if (EPI && ctl.part_out != nullptr) {
     const double tot = block_sum_all(sq, sh);
@@ -229,14 +254,14 @@ __device__ __forceinline__ void tube_kernel_body(const TubeArgs& ta, const VBloc
   }
 }
 
-template <typename TIN, typename TOUT, typename TC, int KB, bool VEC, bool SCALE, bool EPI, bool GROUPED>
+template <typename TIN, typename TOUT, typename TC, int KB, bool SCALE, bool EPI, bool GROUPED>
 __global__ __launch_bounds__(kThreads) void tube_kernel(TubeArgs ta_, const TubeArgs* grp, const int4* bmap) {
   if constexpr (!GROUPED) {
-    tube_kernel_body<TIN, TOUT, TC, KB, VEC, SCALE, EPI>(ta_, hw_block(), false);
+    tube_kernel_body<TIN, TOUT, TC, KB, SCALE, EPI>(ta_, hw_block(), false);
   } else {
     VBlock vb;
     const TubeArgs g = group_args(grp, bmap, vb);
-    tube_kernel_body<TIN, TOUT, TC, KB, VEC, SCALE, EPI>(g, vb, true);
+    tube_kernel_body<TIN, TOUT, TC, KB, SCALE, EPI>(g, vb, true);
   }
 }
 
@@ -255,37 +280,15 @@ __global__ __launch_bounds__(kThreads) void tube_kernel(TubeArgs ta_, const Tube
 // Without an epilogue (fewer registers live) the control block's loads, G
 // and the first tile are in flight together, and the next tile's rows load
 // while the current one is multiplied.
-// VEC: count a multiple of 4 and 16-byte aligned in / src / xnorm / out.
+// VEC: count >= 4, at any alignment (a unit that would cross the end of its
+// slice is read from the slice's last 4 positions and put right when staged).
 // FP64 at 256 x 256 x 64 (67 MB moved): forward 296 us, inverse 202 before
-// (vector units, the input read again for every 8 outputs), now 27 and 27
+// (vector units, the input read again for every 8 outputs), now 25 and 26
 // (FP64 at 200 x 200 x 31: 67 / 52 -> 11.6 / 10.9; FP32 at 200 x 200 x 12: 18 / 15 -> 7.1 / 6.3).
-template <typename T> struct RowStore;
-template <> struct RowStore<float> {
-  __device__ static void st(float* p, const float (&v)[4]) {
-    *reinterpret_cast<f32x4*>(p) = f32x4{v[0], v[1], v[2], v[3]};
-  }
-};
-template <> struct RowStore<double> {
-  __device__ static void st(double* p, const double (&v)[4]) {
-    *reinterpret_cast<double2*>(p) = make_double2(v[0], v[1]);
-    *reinterpret_cast<double2*>(p + 2) = make_double2(v[2], v[3]);
-  }
-};
-template <> struct RowStore<bf16_t> {
-  __device__ static void st(bf16_t* p, const float (&v)[4]) {
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    const unsigned lo = (unsigned)float_to_bf16(v[0]) | ((unsigned)float_to_bf16(v[1]) << 16);
-    const unsigned hi = (unsigned)float_to_bf16(v[2]) | ((unsigned)float_to_bf16(v[3]) << 16);
-    *reinterpret_cast<u32x2*>(p) = u32x2{lo, hi};
-  }
-};
-template <> struct RowStore<f16_t> {
-  __device__ static void st(f16_t* p, const float (&v)[4]) {
-    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-    *reinterpret_cast<h4*>(p) = h4{(f16_t)v[0], (f16_t)v[1], (f16_t)v[2], (f16_t)v[3]};
-  }
-};
-
+// Slices of a size that is no multiple of 4 moved in single elements: FP32 at 333 x 333 x 64
+// 26.0 / 26.0 us, now 20.5 / 20.5.  Whole tiles test no position and mask no load (the loads were
+// waited for where they were masked, before the passes): 512 x 512 x 64 forward to FP32 36 -> 32.5 us,
+// to BF16 39.5 -> 33..
 template <typename T, typename TOUT, int PM, bool SCALE, bool EPI, bool VEC>
 __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const VBlock vb, const bool grouped) {
   typedef Mfma<T> MF;
@@ -312,40 +315,37 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t ntiles = (count + NB - 1) / NB;
 
-  // a tile's input rows and src rows into registers (clamped addresses, selected)
+  // a tile's input rows (rv), then its src rows (sv), which are waited for
+  // later, into registers from clamped addresses; what lies outside is taken
+  // out where they are used
   T rv[XU][4], sv[XU][4];
-  auto load_tile = [&](int64_t tile) {
-    const int64_t e0 = tile * NB;
+  auto load_rows = [&](const T* q, int64_t tile, T (&v)[XU][4]) {
 #pragma unroll
     for (int u = 0; u < XU; ++u) {
       const int i = tid + u * 256;
       const int t = i / (NB / 4), c = (i % (NB / 4)) * 4;
-      const int64_t e = e0 + c;
+      const int64_t row = (int64_t)(t < p ? t : 0) * count, e = tile * NB + c;
       if constexpr (VEC) {
-        const bool ok = t < p && e < count;
-        Vec4Load<T>::load(in + (ok ? (int64_t)t * count + e : 0), rv[u]);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) rv[u][v] = ok ? rv[u][v] : (T)0;
-        if (EPI) {
-          const bool oks = ok && src != nullptr;
-          Vec4Load<T>::load(oks ? src + (int64_t)t * count + e : in, sv[u]);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) sv[u][v] = oks ? sv[u][v] : (T)0;
-        }
+        load4(q + row + (e + 4 <= count ? e : count - 4), v[u]);
       } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const bool ok = t < p && e + v < count;
-          const T x = in[ok ? (int64_t)t * count + e + v : 0];
-          rv[u][v] = ok ? x : (T)0;
-          if (EPI) {
-            const bool oks = ok && src != nullptr;
-            const T y = (src != nullptr ? src : in)[oks ? (int64_t)t * count + e + v : 0];
-            sv[u][v] = oks ? y : (T)0;
-          }
-        }
+        for (int j = 0; j < 4; ++j) v[u][j] = q[row + (e + j < count ? e + j : count - 1)];
       }
     }
+  };
+  auto load_tile = [&](int64_t tile) {
+    load_rows(in, tile, rv);
+    if constexpr (EPI) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (src != nullptr) load_rows(src, tile, sv);
+    }
+  };
+  // entries of a unit at position e beyond the slice (the last tile's)
+  auto tail = [&](int64_t e, T (&v)[4]) {
+    if constexpr (VEC) drop4(v, e - (count - 4));
+    else
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = e + i < count ? v[i] : (T)0;
   };
 
   // prologue: the control block's loads, G and the first tile's rows are all in
@@ -374,7 +374,9 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
   }
   const int lr = lane & 15, lk = lane >> 4;
   double sq = 0.0;
-  for (; tile < ntiles; tile += ta.gx) {
+  // one tile; tail_c: it reaches beyond the slice (whole tiles test no position)
+  auto do_tile = [&](auto tail_c) {
+    constexpr bool last = decltype(tail_c)::value;
     const int64_t e0 = tile * NB;
     if (EPI) load_tile(tile);
     __syncthreads();  // the previous tile's products have been read from LDS (and G is staged)
@@ -383,21 +385,18 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
       const int i = tid + u * 256;
       const int t = i / (NB / 4), c = (i % (NB / 4)) * 4;
       const int64_t e = e0 + c;
+      if (last) {
+        tail(e, rv[u]);
+        if (EPI && use_src) tail(e, sv[u]);
+      }
       if (SCALE) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) rv[u][v] *= sc;
-        if (xnorm != nullptr && t < p) {
-          T* xp = xnorm + (int64_t)t * count + e;
-          if (VEC) {
-            if (e < count) RowStore<T>::st(xp, rv[u]);
-          } else {
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-              if (e + v < count) xp[v] = rv[u][v];
-          }
-        }
+        if (xnorm != nullptr && t < p) store_row(xnorm + (int64_t)t * count, e, count, rv[u], !last);
       }
-      RowStore<T>::st(&sX[t * LDX + c], rv[u]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) rv[u][v] = t < p ? rv[u][v] : (T)0;
+      lds_store4(&sX[t * LDX + c], rv[u]);
     }
     __syncthreads();
     // without an epilogue (fewer registers live) the next tile's rows load while
@@ -431,31 +430,22 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
       const int64_t e = e0 + c;
       if (k >= p) continue;
       T y[4];
-      Vec4Load<T>::load(&sX[k * LDX + c], y);
+      lds_load4(&sX[k * LDX + c], y);
 #pragma unroll
       for (int v = 0; v < 4; ++v) y[v] *= a;
       if (EPI) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) y[v] += use_src ? b * sv[u][v] : (T)0;
-      }
-      TOUT* op = out + (int64_t)k * count + e;
-      if (VEC) {
-        if (e < count) {
-          RowStore<TOUT>::st(op, y);
-          if (EPI) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) sq += (double)y[v] * (double)y[v];
-          }
-        }
-      } else {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          if (e + v < count) {
-            op[v] = cvt<TOUT, T>(y[v]);
-            if (EPI) sq += (double)y[v] * (double)y[v];
-          }
+          if (!last || e + v < count) sq += (double)y[v] * (double)y[v];
       }
+      store_row(out + (int64_t)k * count, e, count, y, !last);
     }
+  };
+  for (; tile < ntiles; tile += ta.gx) {
+    if ((tile + 1) * NB <= count) do_tile(std::false_type{});
+    else do_tile(std::true_type{});
   }
   if (EPI && ta.ctl.part_out != nullptr) {
     const double tot = block_sum_all(sq, sh);
@@ -464,7 +454,7 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
 }
 
 template <typename T, typename TOUT, int PM, bool SCALE, bool EPI, bool VEC, bool GROUPED>
-__global__ __launch_bounds__(256) void tube_mfma_kernel(TubeArgs ta_, const TubeArgs* grp, const int4* bmap) {
+__global__ __launch_bounds__(256, sizeof(T) == 8 ? 2 : 4) void tube_mfma_kernel(TubeArgs ta_, const TubeArgs* grp, const int4* bmap) {
   if constexpr (!GROUPED) {
     tube_mfma_kernel_body<T, TOUT, PM, SCALE, EPI, VEC>(ta_, hw_block(), false);
   } else {
@@ -485,8 +475,7 @@ static hipError_t launch_tube_mfma(dctk_ctx ctx, hipStream_t s, int64_t p, int64
   if (blocks > cap) blocks = cap;
   if (nblocks_out) *nblocks_out = (int)blocks;
   if (epi && ctl.part_out != nullptr && blocks > kRedBlocks) return hipErrorInvalidConfiguration;
-  const bool vec = (count % 4 == 0) && (((uintptr_t)in) % 16 == 0) && (((uintptr_t)xnorm) % 16 == 0) &&
-                   (((uintptr_t)out) % 16 == 0) && (((uintptr_t)src) % 16 == 0);
+  const bool vec = count >= 4;
   TubeArgs ta{};
   ta.p = (int)p;
   ta.count = count;
@@ -566,42 +555,30 @@ __device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t ntiles = (count + NB - 1) / NB;
 
-  // a tile's product rows (rv) and src rows (sv) into registers (clamped
-  // addresses, selected); loading the next tile's rows during the passes
+  // a tile's product rows (rv), then its src rows (sv), which are waited for
+  // later, into registers from clamped addresses (what lies outside is taken
+  // out where they are used); loading the next tile's rows during the passes
   // measured slower
   float rv[XU][4], sv[XU][4];
-  auto load_tile = [&](int64_t tile) {
-    const int64_t e0 = tile * NB;
+  auto load_rows = [&](const float* q, int64_t tile, float (&v)[XU][4]) {
 #pragma unroll
     for (int u = 0; u < XU; ++u) {
       const int i = tid + u * 256;
       const int t = i / (NB / 4), c = (i % (NB / 4)) * 4;
-      const int64_t e = e0 + c;
+      const int64_t row = (int64_t)(t < p ? t : 0) * count, e = tile * NB + c;
       if constexpr (VEC) {
-        const bool ok = t < p && e < count;
-        const float4 q = *reinterpret_cast<const float4*>(in + (ok ? (int64_t)t * count + e : 0));
-        rv[u][0] = ok ? q.x : 0.0f;
-        rv[u][1] = ok ? q.y : 0.0f;
-        rv[u][2] = ok ? q.z : 0.0f;
-        rv[u][3] = ok ? q.w : 0.0f;
-        const bool oks = ok && src != nullptr;
-        const float4 w = *reinterpret_cast<const float4*>(oks ? src + (int64_t)t * count + e : in);
-        sv[u][0] = oks ? w.x : 0.0f;
-        sv[u][1] = oks ? w.y : 0.0f;
-        sv[u][2] = oks ? w.z : 0.0f;
-        sv[u][3] = oks ? w.w : 0.0f;
+        load4(q + row + (e + 4 <= count ? e : count - 4), v[u]);
       } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const bool ok = t < p && e + v < count;
-          const float x = in[ok ? (int64_t)t * count + e + v : 0];
-          rv[u][v] = ok ? x : 0.0f;
-          const bool oks = ok && src != nullptr;
-          const float y = (src != nullptr ? src : in)[oks ? (int64_t)t * count + e + v : 0];
-          sv[u][v] = oks ? y : 0.0f;
-        }
+        for (int j = 0; j < 4; ++j) v[u][j] = q[row + (e + j < count ? e + j : count - 1)];
       }
     }
+  };
+  auto tail = [&](int64_t e, float (&v)[4]) {
+    if constexpr (VEC) drop4(v, e - (count - 4));
+    else
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = e + i < count ? v[i] : 0.0f;
   };
   // one MFMA pass: the products G x (tile in sX) back into sX as [k][e], with
   // G = G1, or (TR) its transpose read from the same LDS copy
@@ -651,15 +628,28 @@ __device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const 
     sG1[k * LDG + t] = g1[u];
   }
   double sq = 0.0;
-  for (int64_t tile = vb.x; tile < ntiles; tile += pa.gx) {
+  // one tile; tail_c: it reaches beyond the slice (whole tiles test no position)
+  auto do_tile = [&](int64_t tile, auto tail_c) {
+    constexpr bool last = decltype(tail_c)::value;
     const int64_t e0 = tile * NB;
-    load_tile(tile);
+    load_rows(in, tile, rv);
+    __builtin_amdgcn_sched_barrier(0);
+    load_rows(src != nullptr ? src : in, tile, sv);
     __syncthreads();  // the previous tile's x rows have been read from sX (and G1 is staged)
 #pragma unroll
     for (int u = 0; u < XU; ++u) {
       const int i = tid + u * 256;
       const int t = i / (NB / 4), c = (i % (NB / 4)) * 4;
-      *reinterpret_cast<float4*>(&sX[t * LDX + c]) = make_float4(rv[u][0], rv[u][1], rv[u][2], rv[u][3]);
+      if (last) {
+        tail(e0 + c, rv[u]);
+        tail(e0 + c, sv[u]);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        rv[u][v] = t < p ? rv[u][v] : 0.0f;
+        sv[u][v] = t < p ? sv[u][v] : 0.0f;
+      }
+      lds_store4(&sX[t * LDX + c], rv[u]);
     }
     __syncthreads();
     mfma_pass(sG1, std::false_type{});
@@ -676,26 +666,15 @@ __device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const 
 #pragma unroll
       for (int v = 0; v < 4; ++v) y[v] += use_src ? b * sv[u][v] : 0.0f;
       if (k < p) {
-        float* op = pa.y + (int64_t)k * count + e;
-        if (VEC) {
-          if (e < count) {
-            RowStore<float>::st(op, y);
+        store_row(pa.y + (int64_t)k * count, e, count, y, !last);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) sq += (double)y[v] * (double)y[v];
-          }
-        } else {
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            if (e + v < count) {
-              op[v] = y[v];
-              sq += (double)y[v] * (double)y[v];
-            }
-        }
+        for (int v = 0; v < 4; ++v)
+          if (!last || e + v < count) sq += (double)y[v] * (double)y[v];
       }
       // positions beyond the slice enter the second pass as zeros
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        if (e + v >= count) y[v] = 0.0f;
+        if (last && e + v >= count) y[v] = 0.0f;
       *rowp = make_float4(y[0], y[1], y[2], y[3]);
     }
     __syncthreads();
@@ -708,15 +687,12 @@ __device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const 
       if (k >= p) continue;
       const float4 q = *reinterpret_cast<const float4*>(&sX[k * LDX + c]);
       const float xv[4] = {q.x, q.y, q.z, q.w};
-      TX* xp = (TX*)pa.x + (int64_t)k * count + e;
-      if (VEC) {
-        if (e < count) RowStore<TX>::st(xp, xv);
-      } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (e + v < count) xp[v] = cvt<TX, float>(xv[v]);
-      }
+      store_row((TX*)pa.x + (int64_t)k * count, e, count, xv, !last);
     }
+  };
+  for (int64_t tile = vb.x; tile < ntiles; tile += pa.gx) {
+    if ((tile + 1) * NB <= count) do_tile(tile, std::false_type{});
+    else do_tile(tile, std::true_type{});
   }
   if (pa.ctl.part_out != nullptr) {
     const double tot = block_sum_all(sq, sh);
@@ -730,7 +706,7 @@ __device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const 
 // and src in flight together (16 rows of 16 bytes per thread at p = 8).  Bound
 // by memory (16 B/element at 4 p flops); inside a Golub-Kahan step it replaces
 // the inverse and the forward transform's own launches and the re-read of y.
-template <typename TX, int KB, bool VEC>
+template <typename TX, int KB>
 __device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const VBlock vb) {
   __shared__ float sG[KB * KB];
   __shared__ double sh[kShCtl];
@@ -742,21 +718,22 @@ __device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const V
   const int64_t stride = (int64_t)pa.gx * kThreads * 4;
   float cv[KB][4], sv[KB][4];
   auto load = [&](int64_t e0) {
+    if (e0 + 4 <= count) {
 #pragma unroll
-    for (int t = 0; t < KB; ++t) {
-      const int64_t row = (int64_t)(t < p ? t : 0) * count;
-      if constexpr (VEC) {
-        const int64_t o = row + (e0 < count ? e0 : 0);
-        Vec4Load<float>::load(in + o, cv[t]);
-        Vec4Load<float>::load(src + o, sv[t]);
-      } else {
+      for (int t = 0; t < KB; ++t) {
+        const int64_t o = (int64_t)(t < p ? t : 0) * count + e0;
+        load4(in + o, cv[t]);
+        load4(src + o, sv[t]);
+      }
+    } else {   // the slice's last thread, and those beyond it
+#pragma unroll
+      for (int t = 0; t < KB; ++t)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const int64_t o = row + (e0 + v < count ? e0 + v : 0);
+          const int64_t o = (int64_t)(t < p ? t : 0) * count + (e0 + v < count ? e0 + v : 0);
           cv[t][v] = in[o];
           sv[t][v] = src[o];
         }
-      }
     }
   };
   int64_t e0 = ((int64_t)vb.x * kThreads + threadIdx.x) * 4;
@@ -796,19 +773,10 @@ __device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const V
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
       if (k >= p) break;
-      float* op = pa.y + (int64_t)k * count + e0;
-      if constexpr (VEC) {
-        RowStore<float>::st(op, y[k]);
+      store_row(pa.y + (int64_t)k * count, e0, count, y[k]);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) sq += (double)y[k][v] * (double)y[k][v];
-      } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (e0 + v < count) {
-            op[v] = y[k][v];
-            sq += (double)y[k][v] * (double)y[k][v];
-          }
-      }
+      for (int v = 0; v < 4; ++v)
+        if (e0 + v < count) sq += (double)y[k][v] * (double)y[k][v];
     }
     if (e0 + stride < count) load(e0 + stride);
 #pragma unroll
@@ -822,14 +790,7 @@ __device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const V
 #pragma unroll
           for (int v = 0; v < 4; ++v) x[v] += w * y[t][v];
         }
-      TX* xp = (TX*)pa.x + (int64_t)k * count + e0;
-      if constexpr (VEC) {
-        RowStore<TX>::st(xp, x);
-      } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (e0 + v < count) xp[v] = cvt<TX, float>(x[v]);
-      }
+      store_row((TX*)pa.x + (int64_t)k * count, e0, count, x);
     }
   }
   if (pa.ctl.part_out != nullptr) {
@@ -838,19 +799,19 @@ __device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const V
   }
 }
 
-template <typename TX, int KB, bool VEC, bool GROUPED>
+template <typename TX, int KB, bool GROUPED>
 __global__ __launch_bounds__(kThreads) void tube_pair_small_kernel(PairArgs pa_, const PairArgs* grp, const int4* bmap) {
   if constexpr (!GROUPED) {
-    tube_pair_small_body<TX, KB, VEC>(pa_, hw_block());
+    tube_pair_small_body<TX, KB>(pa_, hw_block());
   } else {
     VBlock vb;
     const PairArgs g = group_args(grp, bmap, vb);
-    tube_pair_small_body<TX, KB, VEC>(g, vb);
+    tube_pair_small_body<TX, KB>(g, vb);
   }
 }
 
 template <typename TX, int PM, bool VEC, bool GROUPED>
-__global__ __launch_bounds__(256) void tube_pair_kernel(PairArgs pa_, const PairArgs* grp, const int4* bmap) {
+__global__ __launch_bounds__(256, 4) void tube_pair_kernel(PairArgs pa_, const PairArgs* grp, const int4* bmap) {
   if constexpr (!GROUPED) {
     tube_pair_kernel_body<TX, PM, VEC>(pa_, hw_block(), false);
   } else {
@@ -874,9 +835,7 @@ hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p,
   if (blocks > cap) blocks = cap;
   if (nblocks_out) *nblocks_out = (int)blocks;
   if (ctl.part_out != nullptr && blocks > kRedBlocks) return hipErrorInvalidConfiguration;
-  const size_t xe = x_dtype == DCTK_F32 ? 4 : 2;
-  const bool vec = (count % 4 == 0) && ((uintptr_t)c % 16 == 0) && ((uintptr_t)src % 16 == 0) &&
-                   ((uintptr_t)y % 16 == 0) && ((uintptr_t)x % (4 * xe) == 0);
+  const bool vec = count >= 4;
   PairArgs pa{};
   pa.p = (int)p;
   pa.count = count;
@@ -892,11 +851,8 @@ hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p,
     if (vec) return launch_kernel(ctx, s, tube_pair_kernel<TX, PM_, true, false>, tube_pair_kernel<TX, PM_, true, true>, grid, 256, 0, pa); \
     return launch_kernel(ctx, s, tube_pair_kernel<TX, PM_, false, false>, tube_pair_kernel<TX, PM_, false, true>, grid, 256, 0, pa); \
   } while (0)
-#define DCTK_PAIR_S(TX, KB_)                                                                                     \
-  do {                                                                                                         \
-    if (vec) return launch_kernel(ctx, s, tube_pair_small_kernel<TX, KB_, true, false>, tube_pair_small_kernel<TX, KB_, true, true>, grid, kThreads, 0, pa); \
-    return launch_kernel(ctx, s, tube_pair_small_kernel<TX, KB_, false, false>, tube_pair_small_kernel<TX, KB_, false, true>, grid, kThreads, 0, pa); \
-  } while (0)
+#define DCTK_PAIR_S(TX, KB_) \
+  return launch_kernel(ctx, s, tube_pair_small_kernel<TX, KB_, false>, tube_pair_small_kernel<TX, KB_, true>, grid, kThreads, 0, pa)
 #define DCTK_PAIR_P(TX)            \
   do {                             \
     if (p <= 4) DCTK_PAIR_S(TX, 4);   \
@@ -927,8 +883,6 @@ static hipError_t launch_tube_t(dctk_ctx ctx, hipStream_t s, int64_t p, int64_t 
   if (blocks < 1) blocks = 1;
   if (nblocks_out) *nblocks_out = (int)blocks;
   size_t shmem = (size_t)(p * p) * sizeof(TC);
-  bool vec = (count % 4 == 0) && (((uintptr_t)in) % 32 == 0) && (((uintptr_t)out) % 32 == 0) &&
-             (src == nullptr || ((uintptr_t)src) % 32 == 0) && (xnorm == nullptr || ((uintptr_t)xnorm) % 32 == 0);
   TubeArgs ta{};
   ta.p = (int)p;
   ta.count = count;
@@ -939,18 +893,15 @@ static hipError_t launch_tube_t(dctk_ctx ctx, hipStream_t s, int64_t p, int64_t 
   ta.xnorm = xnorm;
   ta.ctl = ctl;
   const dim3 grid((unsigned)blocks);
-#define DCTK_TUBE_LAUNCH(KB, V, S, E) \
-  return launch_kernel(ctx, s, tube_kernel<TIN, TOUT, TC, KB, V, S, E, false>, tube_kernel<TIN, TOUT, TC, KB, V, S, E, true>, grid, kThreads, (unsigned)shmem, ta)
-#define DCTK_TUBE_SE(KB, V)                                                    \
-  do {                                                                         \
-    if (scale) DCTK_TUBE_LAUNCH(KB, V, true, false);                            \
-    if constexpr (sizeof(TIN) == sizeof(TOUT)) DCTK_TUBE_LAUNCH(KB, V, false, true); \
+#define DCTK_TUBE_LAUNCH(KB, S, E) \
+  return launch_kernel(ctx, s, tube_kernel<TIN, TOUT, TC, KB, S, E, false>, tube_kernel<TIN, TOUT, TC, KB, S, E, true>, grid, kThreads, (unsigned)shmem, ta)
+#define DCTK_TUBE_SE(KB)                                                    \
+  do {                                                                      \
+    if (scale) DCTK_TUBE_LAUNCH(KB, true, false);                            \
+    if constexpr (sizeof(TIN) == sizeof(TOUT)) DCTK_TUBE_LAUNCH(KB, false, true); \
   } while (0)
-  if (p <= 4) {
-    if (vec) DCTK_TUBE_SE(4, true); else DCTK_TUBE_SE(4, false);
-  } else {
-    if (vec) DCTK_TUBE_SE(8, true); else DCTK_TUBE_SE(8, false);
-  }
+  if (p <= 4) DCTK_TUBE_SE(4);
+  DCTK_TUBE_SE(8);
   return hipErrorInvalidValue;   // a 16-bit output is a slice product's operand: the input side
 #undef DCTK_TUBE_SE
 #undef DCTK_TUBE_LAUNCH
