@@ -821,17 +821,18 @@ static hipError_t gkb_step_merged(dctk_ctx ctx, dctk_krylov ws, int j, bool pend
     // unnormalised vector it has just written), so only the first step of a
     // run has a forward transform of its own.  A pending update is evaluated
     // by the first paired kernel of the step, after the forward GEMM (the
-    // GEMM's input is alpha_j V_j transformed; 1/alpha_j joins the epilogue).
+    // GEMM's input is alpha_j V_j transformed, times a power of two; 1/alpha_j
+    // and that power's inverse join the epilogue).
     // (one schedule point per product, as on the other paths, so batches of
     // mixed paths stay aligned step by step)
     rec_phase(ctx);
     if ((e = pending ? pair_gemm(op, ctx->stream, 0, c1) : pair_first(op, ctx->stream, 0, Vj, c1)) != hipSuccess)
       return e;
-    if ((e = pair_transforms(op, ctx->stream, 0, Uj, Un, c1, &npA)) != hipSuccess) return e;
+    if ((e = pair_transforms(op, ctx->stream, 0, Uj, Un, pending, c1, &npA)) != hipSuccess) return e;
     c2.npart_in = npA;
     rec_phase(ctx);
     if ((e = pair_gemm(op, ctx->stream, 1, c2)) != hipSuccess) return e;
-    if ((e = pair_transforms(op, ctx->stream, 1, Vj, Vn, c2, &npB)) != hipSuccess) return e;
+    if ((e = pair_transforms(op, ctx->stream, 1, Vj, Vn, true, c2, &npB)) != hipSuccess) return e;
     ws->last_npart = npB;
     return hipSuccess;
   }

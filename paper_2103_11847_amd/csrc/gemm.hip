@@ -1100,8 +1100,7 @@ static hipError_t slice_gemms(dctk_op op, hipStream_t s, int adjoint, const Gate
 
 bool pair_eligible(dctk_op op) {
   // short tubes only with FP32 slice products: pairing rounds the next product's
-  // input from the unnormalised vector, whose scale FP16 does not bear as well
-  // as the normalised one's, and 16-bit short-tube solves keep their roundings
+  // input from the unnormalised vector, and 16-bit short-tube solves keep their roundings
   if (op->p < 16 && op->gemm_dtype != DCTK_F32) return false;
   return !op->fast && tube_pair_ok(op->p, op->vec_dtype) &&
          !(fused_eligible(op) && (use_fused(op, 0) || use_fused(op, 1)));
@@ -1124,8 +1123,8 @@ hipError_t pair_gemm(dctk_op op, hipStream_t s, int adjoint, const Ctl& ctl) {
   return slice_gemms(op, s, adjoint, gemm_gate(ctl));
 }
 
-hipError_t pair_transforms(dctk_op op, hipStream_t s, int adjoint, const void* src, void* Y, const Ctl& ctl,
-                           int* nblocks_out) {
+hipError_t pair_transforms(dctk_op op, hipStream_t s, int adjoint, const void* src, void* Y, bool xin,
+                           const Ctl& ctl, int* nblocks_out) {
   dctk_ctx ctx = op->ctx;
   const int64_t pp = op->p * op->p;
   const int64_t rout = adjoint ? op->n2 : op->n1;
@@ -1135,7 +1134,7 @@ hipError_t pair_transforms(dctk_op op, hipStream_t s, int adjoint, const void* s
   const int g1 = adjoint ? 3 : 1;
   prof_begin(ctx, PROF_TUBE_PAIR);
   hipError_t e = launch_tube_pair(ctx, s, op->gemm_dtype, op->p, rout * op->s, (const float*)op->ch,
-                                  (const float*)src, (float*)Y, op->xh, op->Gf + g1 * pp, ctl, nblocks_out);
+                                  (const float*)src, (float*)Y, op->xh, op->Gf + g1 * pp, xin, ctl, nblocks_out);
   prof_end(ctx, PROF_TUBE_PAIR);
   return e;
 }

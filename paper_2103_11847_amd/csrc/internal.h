@@ -742,9 +742,10 @@ hipError_t launch_tube(dctk_ctx ctx, hipStream_t st, int in_dtype, int out_dtype
 // by the control block's input scale; partials of y^2 in ctl.part_out), paired with
 // the next product's forward transform x = G1^T y in x_dtype (FP32 vectors, p <= 64).
 // G1 is L^{-1} after a forward product (then G1^T = L^{-T}), L^T after an adjoint (G1^T = L).
+// x carries the inverse of the power of two below alpha_1 (ctl.st); xin: so does the operand of c.
 bool tube_pair_ok(int64_t p, int vec_dtype);
 hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p, int64_t count, const float* c,
-                            const float* src, float* y, void* x, const float* G1, const Ctl& ctl,
+                            const float* src, float* y, void* x, const float* G1, bool xin, const Ctl& ctl,
                             int* nblocks_out);
 
 // C_k = op(A_k) op(B_k), batched over `batch`; tile 0: by problem size, else 32/64/128
@@ -773,12 +774,13 @@ hipError_t apply_op(dctk_op op, hipStream_t s, int adjoint, const void* X, void*
 // pair_gemm the slice GEMMs of a product whose transformed input is already in
 // place; pair_transforms the product's inverse transform with its epilogue
 // (Y = a M(.) + b src under ctl, partials of Y^2) paired with the forward
-// transform of the next product (the other direction), whose input is Y.
+// transform of the next product (the other direction), whose input is Y
+// (xin: this product's input came from such a pair, not from pair_first).
 bool pair_eligible(dctk_op op);
 hipError_t pair_first(dctk_op op, hipStream_t s, int adjoint, const void* X, const Ctl& ctl);
 hipError_t pair_gemm(dctk_op op, hipStream_t s, int adjoint, const Ctl& ctl);
-hipError_t pair_transforms(dctk_op op, hipStream_t s, int adjoint, const void* src, void* Y, const Ctl& ctl,
-                           int* nblocks_out);
+hipError_t pair_transforms(dctk_op op, hipStream_t s, int adjoint, const void* src, void* Y, bool xin,
+                           const Ctl& ctl, int* nblocks_out);
 
 // ---- streaming vector kernels (vec.hip) ------------------------------------
 // partials of sum(x . z) (z null: x . x)

@@ -8,6 +8,7 @@
 // longer than 8 run on the matrix cores.  The work is HBM-bound for the p of
 // colour images and video (2p flops per 2 elements moved).
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "mfma.h"
@@ -521,9 +522,17 @@ static hipError_t launch_tube_mfma(dctk_ctx ctx, hipStream_t s, int64_t p, int64
 // of the first transform's product; the scale it returns for that product's
 // input (1/alpha or 1/beta, as the input x of that product was stored
 // unnormalised) joins `a`.
+// x is stored as 2^-e G1^T y, 2^e the power of two below alpha_1, and the
+// product's own pair (xin) multiplies `a` by 2^e: y has the operator's scale, so
+// the slice product of G1^T y would hold the square of it, which FP32 does not
+// from 1e-19 down and 1e19 up.  alpha_1 stands for y's norm, which is known only
+// after the launch; a power of two leaves every bit in between as it was.  FP16
+// operands, whose narrow range would turn a small alpha_1 into infinities, keep
+// y's own scale (e = 0).
 struct PairArgs {
   int gx, gy, gz;
   int p;
+  int xin;           // 1: the slice products' operand carries 2^-e
   int64_t count;
   const float* c;    // p x count slice products (FP32)
   const float* src;  // p x count, or null
@@ -532,6 +541,13 @@ struct PairArgs {
   const float* G1;   // p x p
   Ctl ctl;
 };
+
+// e of PairArgs from alpha_1, within what FP32 powers of two reach
+__device__ inline int pair_exp(double alpha1) {
+  const int e = (int)((__builtin_bit_cast(unsigned long long, alpha1) >> 52) & 0x7ff) - 1023;
+  return __builtin_amdgcn_readfirstlane(e < -120 ? -120 : (e > 120 ? 120 : e));
+}
+__device__ inline float pow2f(int e) { return __builtin_bit_cast(float, (127 + e) << 23); }
 
 template <typename TX, int PM, bool VEC>
 __device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const VBlock vb, const bool grouped) {
@@ -609,6 +625,7 @@ __device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const 
   };
 
   // prologue: the control block's loads and the matrix in flight together
+  const double alpha1 = pa.ctl.st->alpha[0];
   const CtlLoad cl = ctl_load(pa.ctl);
   float g1[GU];
 #pragma unroll
@@ -620,7 +637,9 @@ __device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const 
   }
   double a_d, b_d, s_d;
   if (!ctl_eval(pa.ctl, cl, a_d, b_d, s_d, sh, vb)) return;
-  const float a = (float)(a_d * s_d), b = (float)b_d;
+  const int ex = std::is_same<TX, f16_t>::value ? 0 : pair_exp(alpha1);
+  const float xs = pow2f(-ex), b = (float)b_d;
+  const float a = (float)(a_d * s_d * (double)(pa.xin ? pow2f(ex) : 1.0f));
   const bool use_src = src != nullptr && b != 0.0f;   // b = 0: src never enters
 #pragma unroll
   for (int u = 0; u < GU; ++u) {
@@ -674,7 +693,7 @@ __device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const 
       // positions beyond the slice enter the second pass as zeros
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        if (last && e + v >= count) y[v] = 0.0f;
+        y[v] = last && e + v >= count ? 0.0f : xs * y[v];
       *rowp = make_float4(y[0], y[1], y[2], y[3]);
     }
     __syncthreads();
@@ -738,13 +757,16 @@ __device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const V
   };
   int64_t e0 = ((int64_t)vb.x * kThreads + threadIdx.x) * 4;
   // the first tubes, the matrix and the control block's values in flight together
+  const double alpha1 = pa.ctl.st->alpha[0];
   const CtlLoad cl = ctl_load(pa.ctl);
   const int gi = (int)threadIdx.x;
   const float g = pa.G1[gi < p * p ? gi : 0];
   load(e0);
   double a_d, b_d, s_d;
   if (!ctl_eval(pa.ctl, cl, a_d, b_d, s_d, sh, vb)) return;
-  const float a = (float)(a_d * s_d), b = has_src ? (float)b_d : 0.0f;
+  const int ex = std::is_same<TX, f16_t>::value ? 0 : pair_exp(alpha1);
+  const float xs = pow2f(-ex), b = has_src ? (float)b_d : 0.0f;
+  const float a = (float)(a_d * s_d * (double)(pa.xin ? pow2f(ex) : 1.0f));
   const bool use_src = b != 0.0f;   // b = 0: src never enters
   if (gi < p * p) sG[gi / p * KB + gi % p] = g;
   __syncthreads();
@@ -790,6 +812,8 @@ __device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const V
 #pragma unroll
           for (int v = 0; v < 4; ++v) x[v] += w * y[t][v];
         }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[v] *= xs;
       store_row((TX*)pa.x + (int64_t)k * count, e0, count, x);
     }
   }
@@ -824,7 +848,7 @@ __global__ __launch_bounds__(256, 4) void tube_pair_kernel(PairArgs pa_, const P
 bool tube_pair_ok(int64_t p, int vec_dtype) { return vec_dtype == DCTK_F32 && p <= kMaxTube; }
 
 hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p, int64_t count, const float* c,
-                            const float* src, float* y, void* x, const float* G1, const Ctl& ctl,
+                            const float* src, float* y, void* x, const float* G1, bool xin, const Ctl& ctl,
                             int* nblocks_out) {
   if (!tube_pair_ok(p, DCTK_F32)) return hipErrorInvalidValue;
   // four workgroups per CU (36 KB of LDS each), each walking several tiles of
@@ -838,6 +862,7 @@ hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p,
   const bool vec = count >= 4;
   PairArgs pa{};
   pa.p = (int)p;
+  pa.xin = xin ? 1 : 0;
   pa.count = count;
   pa.c = c;
   pa.src = src;
