@@ -472,7 +472,25 @@ static int op_create_impl(dctk_ctx ctx, int tube, int gemm_dtype, int nd, const 
     }
   }
 #undef DCTK_TUBE_F64
+  // the range of the FP32 operands (the slice GEMM's OperandRange)
+  static_assert(2 * 2 * kRangeBlocks * sizeof(unsigned) <= sizeof(double) * kRedBlocks, "fits the scratch");
+  unsigned range[2][kRangeBlocks][2];
+  const int ops = gemm_dtype == DCTK_F32 ? 1 + op->two_sided : 0;
+  for (int o = 0; o < ops; ++o) {
+    unsigned* dev = (unsigned*)ctx->red_partials + o * 2 * kRangeBlocks;
+    DCTK_TRY(launch_range(ctx, o ? p * s * s : p * n1 * n2, (const float*)(o ? op->Bh : op->Ah), dev));
+    DCTK_TRY(hipMemcpyAsync(range[o], dev, sizeof(range[o]), hipMemcpyDeviceToHost, ctx->stream));
+  }
   DCTK_TRY(hipStreamSynchronize(ctx->stream));
+  for (int o = 0; o < ops && e == hipSuccess; ++o) {
+    unsigned hi = 0, lo = ~0u;
+    for (int b = 0; b < kRangeBlocks; ++b) {
+      hi = std::max(hi, range[o][b][0]);
+      lo = std::min(lo, range[o][b][1]);
+    }
+    memcpy(&op->top[o], &hi, sizeof(float));
+    op->small[o] = lo < kSplitLow - 1u;
+  }
 #undef DCTK_TRY
   if (tmp) (void)hipFree(tmp);
   if (e != hipSuccess) {
@@ -514,7 +532,8 @@ int dctk_op_autotune(dctk_ctx ctx, dctk_op op, int reps, int* choice) {
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t e = hipMalloc(&X, bytes);
   if (e == hipSuccess) e = hipMalloc(&Y, bytes);
-  if (e == hipSuccess) e = hipMemsetAsync(X, 0, bytes, ctx->stream);
+  // (FP32 ones, FP64 2^-7: zeros would be data of their own kind to the GEMMs)
+  if (e == hipSuccess) e = hipMemsetD32Async((hipDeviceptr_t)X, 0x3f800000, bytes / 4, ctx->stream);
   if (e == hipSuccess) e = hipEventCreate(&e0);
   if (e == hipSuccess) e = hipEventCreate(&e1);
   Ctl c{};

@@ -31,6 +31,7 @@ struct GemmArgs {
   void* C;
   int64_t ldc, sC;
   Gate g;
+  OperandRange range;   // FP32
   int nbatch;   // > 0: slices placed per XCD (see slice_block); the grid's z is padded to 8 ceil(nbatch / 8)
 };
 
@@ -645,9 +646,18 @@ __global__ __launch_bounds__(256) void gemm_mn_kernel(GemmArgs ga_, const GemmAr
 //
 // The split does not represent infinities and NaN (their remainders are NaN),
 // values that round to infinity in bfloat16, nor all 24 bits of numbers below
-// 2^-110.  A wave whose largest result is not finite, or not zero and below
-// 2^-96, computes its part again with the FP32 instruction (split_redo), in
-// the order of gemm_mn_kernel.
+// 2^-110 (the third part ends at 2^-133: such a number loses up to 2^-134).  A
+// tile in which that may show is computed again with the FP32 instruction, in
+// the order of gemm_mn_kernel (split_again): where a result is not finite, and
+// where K losses, times the largest number they can meet, reach 2^-26 of a
+// result.  For losses of the data that number is the operator's largest, known
+// since its creation, so only tiles with small results or zeros look at their
+// data; an operator that holds such numbers has every tile do so.  In a Krylov
+// step the data is of norm 1 and neither is needed.  No number is tested in the
+// loop (that cost 49 -> 54 us at 3 x 1024^3), and results that are merely small
+// cost nothing: the BF16 instruction keeps subnormal operands and results.
+// 64 x 512^3: 106 us, 126 where every tile looks at its data, 290 where
+// every tile is computed again; 3 x 1024^3: 49, 59 and 140 us.
 struct Split8 {
   uint4 h[3];
 };
@@ -679,36 +689,145 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t float_buffer(const float* p, i
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, (int)(n * 4), 0x00020000);
 }
 
-// A wave's FM x FN blocks from row m0, column n0 with the FP32 instruction,
-// operands straight from memory: rarely run, so kept small.
-template <int FM, int FN, bool TB>
-__device__ __forceinline__ void split_redo(const float* A, const float* B, float* C, int M, int N, int K, int64_t lda,
-                                        int64_t ldb, int64_t ldc, int m0, int n0) {
-  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
-#pragma unroll 1
-  for (int i = 0; i < FM; ++i)
-#pragma unroll 1
-    for (int j = 0; j < FN; ++j) {
-      const int m = m0 + i * 16 + lr, n = n0 + j * 16 + lr;
-      f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-      for (int ks = 0; ks < K; ks += 4) {
-        const int k = ks + lk;
-        const bool oka = m < M && k < K, okb = n < N && k < K;
-        const float av = A[oka ? (int64_t)m * lda + k : 0];
-        const float bv = B[okb ? (TB ? (int64_t)n * ldb + k : (int64_t)k * ldb + n) : 0];
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(oka ? av : 0.0f, okb ? bv : 0.0f, acc, 0, 0, 0);
+typedef __attribute__((address_space(3))) float lds_float;
+typedef __attribute__((address_space(3))) unsigned lds_uint;
+constexpr int kSplitSeen = 5;
+// twice the bits of the least magnitude to which K losses of 2^-134 times `top` stay below 2^-26
+__device__ inline unsigned split_reach(int K, float top) {
+  return 2u * __builtin_bit_cast(unsigned, 0x1p-108f * (float)K * top);
+}
+
+// What follows a tile whose results may show a loss (seen[0]: one is not finite,
+// seen[1]: one is within reach of the data's), or whose operator holds numbers
+// that lose bits: the tile's data is read for its largest magnitude (seen[2])
+// and numbers that lose bits (seen[3]), and if a result is within reach of
+// either's losses, the tile is computed again with the FP32 instruction,
+// operands staged as they are.  `least` is twice the bits of the least magnitude
+// among the lane's results.  Nothing of the split loop is taken over, the
+// arguments neither (they are read again through gp): what both would share
+// cost registers in the loop (14.7 -> 15.9 us at 31 x 243 x 211 x 197).
+template <int BM, int BN, int NT, int WGM, int WGN, bool TB>
+__device__ __forceinline__ void split_again(const GemmArgs* gp, int bx, int by, int bz, unsigned least, lds_float* As,
+                                            lds_float* Bs, lds_uint* seen) {
+  constexpr int BK = 32, LD = BK + 4;
+  constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 16, FN = WN / 16;
+  static_assert(LD <= 3 * BK / 2, "the rows fit the three planes");
+  const GemmArgs& ga = *gp;
+  const int M = ga.M, N = ga.N, K = ga.K;
+  const int64_t lda = ga.lda, ldb = ga.ldb;
+  const int m0 = by * BM, n0 = bx * BN;
+  const float* A = (const float*)ga.A + (int64_t)bz * ga.sA;
+  const float* B = (const float*)ga.B + (int64_t)bz * ga.sB;
+  float* C = (float*)ga.C + (int64_t)bz * ga.sC;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave / WGN, wn = wave % WGN, lr = lane & 15, lg = lane >> 4;
+
+  if (seen[0] == 0) {
+    unsigned top = 0, low = ~0u;   // twice the bits of the largest magnitude, of the least above 0 minus 1
+    auto see = [&](float x) {
+      const unsigned t = __builtin_bit_cast(unsigned, x) << 1;
+      top = max(top, t);
+      low = min(low, t - 1u);
+    };
+    // four elements of a row from i, or its last four (no branch per load: it would be waited for)
+    auto see4 = [&](const float* row, int i, int len) {
+      typedef float f32x4_un __attribute__((ext_vector_type(4), aligned(4)));
+      const f32x4_un v = *reinterpret_cast<const f32x4_un*>(row + min(i, len - 4));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float x = v[q];
+        see(x);
       }
-      if (n >= N) continue;
+    };
+    const int rows = min(BM, M - m0);
+    if (!ga.range.right && N >= 4) {          // columns of B (never TB)
+      constexpr int TPR = BN / 4;
+#pragma unroll 16
+      for (int k = tid / TPR; k < K; k += NT / TPR) see4(B + (int64_t)k * ldb, n0 + tid % TPR * 4, N);
+    } else if (ga.range.right && K >= 4) {    // rows of A
+      const int units = (K + 3) / 4;
+      int r = tid / units, q = tid % units;
+#pragma unroll 8
+      for (int i = tid; i < rows * units; i += NT) {
+        see4(A + (int64_t)(m0 + r) * lda, q * 4, K);
+        q += NT;
+        const int rr = q / units;
+        r += rr;
+        q -= rr * units;
+      }
+    } else if (!ga.range.right) {
+      for (int i = tid; i < K * N; i += NT) see(B[(int64_t)(i / N) * ldb + i % N]);
+    } else {
+      for (int i = tid; i < rows * K; i += NT) see(A[(int64_t)(m0 + i / K) * lda + i % K]);
+    }
+    for (int d = 32; d > 0; d >>= 1) top = max(top, (unsigned)__shfl_xor((int)top, d));
+    if (lane == 0) __hip_atomic_fetch_max(&seen[2], top >> 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (__any(low < 2u * kSplitLow - 1u)) seen[3] = 1;
+    __syncthreads();
+    if (ga.range.small != 0 && __any(least < split_reach(K, __builtin_bit_cast(float, seen[2])))) seen[4] = 1;
+    __syncthreads();
+    if (seen[4] == 0 && (seen[1] == 0 || seen[3] == 0)) return;
+  }
+
+  f32x4 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  // a chunk's operands in registers while the one before is multiplied; rows
+  // and columns beyond an operand repeat its last one, k beyond K are zeros
+  constexpr int RA = BM * BK / NT, RB = BN * BK / NT;
+  const int kk = tid % BK, r0 = tid / BK, kb = tid / BN, cb = min(n0 + tid % BN, N - 1);
+  float ra[RA], rb[RB];
+  auto load = [&](int k0) {
+    const int ka = min(k0 + kk, K - 1);
+#pragma unroll
+    for (int u = 0; u < RA; ++u) ra[u] = A[(int64_t)min(m0 + r0 + u * (NT / BK), M - 1) * lda + ka];
+#pragma unroll
+    for (int u = 0; u < RB; ++u)
+      rb[u] = TB ? B[(int64_t)min(n0 + r0 + u * (NT / BK), N - 1) * ldb + ka]
+                 : B[(int64_t)min(k0 + kb + u * (NT / BN), K - 1) * ldb + cb];
+  };
+  load(0);
+  for (int k0 = 0; k0 < K; k0 += BK) {
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < RA; ++u) As[(r0 + u * (NT / BK)) * LD + kk] = k0 + kk < K ? ra[u] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < RB; ++u) {
+      const int k = TB ? kk : kb + u * (NT / BN), c = TB ? r0 + u * (NT / BK) : tid % BN;
+      Bs[c * LD + k] = k0 + k < K ? rb[u] : 0.0f;
+    }
+    __syncthreads();
+    if (k0 + BK < K) load(k0 + BK);
+#pragma unroll 2
+    for (int ks = 0; ks < BK; ks += 4) {
+      float bf[FN];
+#pragma unroll
+      for (int j = 0; j < FN; ++j) bf[j] = Bs[(wn * WN + j * 16 + lr) * LD + ks + lg];
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        const float af = As[(wm * WM + i * 16 + lr) * LD + ks + lg];
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af, bf[j], acc[i][j], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int col = n0 + wn * WN + j * 16 + lr;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = m0 + i * 16 + lk * 4 + r;
-        if (row < M) C[(int64_t)row * ldc + n] = acc[r];
+        const int row = m0 + wm * WM + i * 16 + lg * 4 + r;
+        if (row < M && col < N) C[(int64_t)row * ga.ldc + col] = acc[i][j][r];
       }
     }
 }
 
 template <int BM, int BN, int NT, int WGM, int WGN, bool TB>
-__device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const VBlock vb) {
+__device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const GemmArgs* gp, const VBlock vb) {
   constexpr int BK = 32;
   constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 16, FN = WN / 16;
   constexpr int AU = BM * 4 / NT, BU = BN * 4 / NT;   // 8-element units per thread and chunk
@@ -717,6 +836,7 @@ __device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const
   if (!gate_open(ga.g)) return;
   __shared__ uint4 As[3][BM * 4];
   __shared__ uint4 Bs[3][BN * 4];
+  __shared__ unsigned seen[kSplitSeen];
   const int M = ga.M, N = ga.N, K = ga.K;
   const float* A = (const float*)ga.A + (int64_t)vb.z * ga.sA;
   const float* B = (const float*)ga.B + (int64_t)vb.z * ga.sB;
@@ -792,6 +912,7 @@ __device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const
     for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
   load_chunk(0);
+  if (tid < kSplitSeen) seen[tid] = 0;
   for (int k0 = 0; k0 < K; k0 += BK) {
     __syncthreads();
     store_chunk();
@@ -819,7 +940,33 @@ __device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const
     }
   }
 
-  unsigned big = 0;   // bits of the largest magnitude (infinities and NaN above all finite ones)
+  // The least and the largest of twice the results' magnitudes in bits (rows
+  // beyond the operand are zeros; columns beyond it are the next row's data, and
+  // may stay).  Agreed on before the results leave: a barrier after the stores
+  // would wait for them.
+  unsigned least = ~0u, most = 0;
+  auto look = [&](auto edge_c) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        unsigned l = ~0u;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          const float v = acc[i][j][r];
+          const unsigned t = __builtin_bit_cast(unsigned, v) << 1;
+          l = min(l, t);
+          most = max(most, t);
+        }
+        if (decltype(edge_c)::value) l = m0 + wm * WM + i * 16 + lg * 4 + r < M ? l : ~0u;
+        least = min(least, l);
+      }
+  };
+  if (m0 + BM <= M) look(std::false_type{});
+  else look(std::true_type{});
+  if (__any(most >= 0xff000000u)) seen[0] = 1;
+  if (__any(least < split_reach(K, ga.range.top))) seen[1] = 1;
+  __syncthreads();
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -828,15 +975,12 @@ __device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = m0 + wm * WM + i * 16 + lg * 4 + r;
-        const float v = acc[i][j][r];
-        const unsigned mag = __builtin_bit_cast(unsigned, v) & 0x7fffffffu;
-        big = big > mag ? big : mag;
-        if (row < M && col < N) C[(int64_t)row * ga.ldc + col] = v;
+        if (row < M && col < N) C[(int64_t)row * ga.ldc + col] = acc[i][j][r];
       }
     }
-  const bool high = big >= 0x7f800000u, some = big != 0, normal = big >= (127u - 96u) << 23;
-  if (__any(high) || (__any(some) && !__any(normal)))
-    split_redo<FM, FN, TB>(A, B, C, M, N, K, ga.lda, ga.ldb, ga.ldc, m0 + wm * WM, n0 + wn * WN);
+  if ((seen[0] | seen[1]) != 0 || ga.range.small != 0)
+    split_again<BM, BN, NT, WGM, WGN, TB>(gp, vb.x, vb.y, vb.z, least, (lds_float*)&As[0][0], (lds_float*)&Bs[0][0],
+                                          (lds_uint*)seen);
 }
 
 template <int BM, int BN, int NT, int WGM, int WGN, bool TB, bool GROUPED>
@@ -844,12 +988,13 @@ __global__ __launch_bounds__(NT, BM == 64 ? 4 : 2) void gemm_split_kernel(GemmAr
   if constexpr (!GROUPED) {
     VBlock vb = hw_block();
     if (!slice_block(ga_, vb)) return;
-    gemm_split_kernel_body<BM, BN, NT, WGM, WGN, TB>(ga_, vb);
+    // (the arguments where the kernel finds them: the first one, from the segment's start)
+    gemm_split_kernel_body<BM, BN, NT, WGM, WGN, TB>(ga_, (const GemmArgs*)__builtin_amdgcn_kernarg_segment_ptr(), vb);
   } else {
     VBlock vb;
     const GemmArgs g = group_args(grp, bmap, vb);
     if (!slice_block(g, vb)) return;   // the instance's grid may be padded
-    gemm_split_kernel_body<BM, BN, NT, WGM, WGN, TB>(g, vb);
+    gemm_split_kernel_body<BM, BN, NT, WGM, WGN, TB>(g, grp + bmap[blockIdx.x].x, vb);
   }
 }
 
@@ -915,8 +1060,10 @@ static int split_tile(int M, int N, int batch, int num_cus) {
 template <typename T>
 static hipError_t launch_gemm_vec(dctk_ctx ctx, hipStream_t s, int M, int N, int K, const void* A, int64_t lda,
                                   int64_t sA, int ta, const void* B, int64_t ldb, int64_t sB, int tb, void* C,
-                                  int64_t ldc, int64_t sC, int batch, Gate g, int num_cus, int tile) {
+                                  int64_t ldc, int64_t sC, int batch, Gate g, int num_cus, int tile,
+                                  const OperandRange& range) {
   GemmArgs ga{};
+  ga.range = range;
   ga.M = M;
   ga.N = N;
   ga.K = K;
@@ -1005,13 +1152,13 @@ static int g_num_cus = 256;
 hipError_t launch_gemm(dctk_ctx ctx, hipStream_t s, int in_dtype, int out_acc, int M, int N, int K,
                        const void* A, int64_t lda, int64_t sA, int ta,
                        const void* B, int64_t ldb, int64_t sB, int tb,
-                       void* C, int64_t ldc, int64_t sC, int batch, Gate g, int tile) {
+                       void* C, int64_t ldc, int64_t sC, int batch, Gate g, int tile, const OperandRange& range) {
   // out_acc = 1: output in the accumulator type; 0: output in the input type
   switch (in_dtype) {
     case DCTK_F64:
-      return launch_gemm_vec<double>(ctx, s, M, N, K, A, lda, sA, ta, B, ldb, sB, tb, C, ldc, sC, batch, g, g_num_cus, tile);
+      return launch_gemm_vec<double>(ctx, s, M, N, K, A, lda, sA, ta, B, ldb, sB, tb, C, ldc, sC, batch, g, g_num_cus, tile, range);
     case DCTK_F32:
-      return launch_gemm_vec<float>(ctx, s, M, N, K, A, lda, sA, ta, B, ldb, sB, tb, C, ldc, sC, batch, g, g_num_cus, tile);
+      return launch_gemm_vec<float>(ctx, s, M, N, K, A, lda, sA, ta, B, ldb, sB, tb, C, ldc, sC, batch, g, g_num_cus, tile, range);
     case DCTK_BF16:
       if (out_acc)
         return launch_gemm_t<bf16_t, float>(ctx, s, M, N, K, A, lda, sA, ta, B, ldb, sB, tb, C, ldc, sC, batch, g, g_num_cus, tile);
@@ -1066,7 +1213,10 @@ static Gate gemm_gate(const Ctl& ctl) {
 }
 
 // Step 2 of a three-kernel product: the slice products of X~ (op->xh) into op->ch.
-static hipError_t slice_gemms(dctk_op op, hipStream_t s, int adjoint, const Gate& g) {
+// In a Krylov step X~ is that of a vector of norm 1, or near it: what the FP32
+// operands lose below 2^-110 is then far below the product's rounding, unless
+// the operator itself is that small, and nothing has to be looked for.
+static hipError_t slice_gemms(dctk_op op, hipStream_t s, int adjoint, const Ctl& ctl) {
   dctk_ctx ctx = op->ctx;
   const int tile = op->tune[adjoint ? 1 : 0][1];
   const int64_t p = op->p, n1 = op->n1, n2 = op->n2, sc = op->s;
@@ -1082,17 +1232,22 @@ static hipError_t slice_gemms(dctk_op op, hipStream_t s, int adjoint, const Gate
   const void* Aop = tcopy ? op->AhT : op->Ah;
   const int64_t ldA = tcopy ? n1 : n2;
   const int tA = adjoint && !tcopy ? 1 : 0;
+  const Gate g = gemm_gate(ctl);
+  const bool unit = ctl.kind != CTL_PLAIN && op->top[0] >= 0x1p-40f && (!op->two_sided || op->top[1] >= 0x1p-40f);
+  const OperandRange ra = unit ? OperandRange{0.0f, 0, 0} : OperandRange{op->top[0], op->small[0], 0};
+  const OperandRange rb = unit ? OperandRange{0.0f, 0, 1} : OperandRange{op->top[1], op->small[1], 1};
   if (!op->two_sided) {
     // forward: (n1 x n2)(n2 x s);  adjoint: (n2 x n1 := A~^T)(n1 x s)
     e = launch_gemm(ctx, s, gdt, 1, (int)rout, (int)sc, (int)rin, Aop, ldA, sAh, tA,
-                    op->xh, sc, rin * sc, 0, op->ch, sc, rout * sc, (int)p, g, tile);
+                    op->xh, sc, rin * sc, 0, op->ch, sc, rout * sc, (int)p, g, tile, ra);
   } else {
     e = launch_gemm(ctx, s, gdt, 0, (int)rout, (int)sc, (int)rin, Aop, ldA, sAh, tA,
-                    op->xh, sc, rin * sc, 0, op->th, sc, rout * sc, (int)p, g, tile);
+                    op->xh, sc, rin * sc, 0, op->th, sc, rout * sc, (int)p, g, tile, ra);
     // right factor: forward (rout x s)(s x s) with B~; adjoint with B~^T
     if (e == hipSuccess)
       e = launch_gemm(ctx, s, gdt, 1, (int)rout, (int)sc, (int)sc, op->th, sc, rout * sc, 0,
-                      op->Bh, sc, sc * sc, adjoint ? 1 : 0, op->ch, sc, rout * sc, (int)p, g, tile);
+                      op->Bh, sc, sc * sc, adjoint ? 1 : 0, op->ch, sc, rout * sc, (int)p, g, tile,
+                      rb);
   }
   prof_end(ctx, PROF_GEMM);
   return e;
@@ -1116,11 +1271,11 @@ hipError_t pair_first(dctk_op op, hipStream_t s, int adjoint, const void* X, con
                              op->Gf + gi * pp, nullptr, nullptr, ctl, true, false, nullptr);
   prof_end(ctx, PROF_TUBE_FWD);
   if (e != hipSuccess) return e;
-  return slice_gemms(op, s, adjoint, gemm_gate(ctl));
+  return slice_gemms(op, s, adjoint, ctl);
 }
 
 hipError_t pair_gemm(dctk_op op, hipStream_t s, int adjoint, const Ctl& ctl) {
-  return slice_gemms(op, s, adjoint, gemm_gate(ctl));
+  return slice_gemms(op, s, adjoint, ctl);
 }
 
 hipError_t pair_transforms(dctk_op op, hipStream_t s, int adjoint, const void* src, void* Y, bool xin,
@@ -1168,7 +1323,7 @@ hipError_t apply_op(dctk_op op, hipStream_t s, int adjoint, const void* X, void*
   Ctl later = ctl;
   later.from_state = 1;
   // step 2: slice products
-  e = slice_gemms(op, s, adjoint, gemm_gate(ctl));
+  e = slice_gemms(op, s, adjoint, ctl);
   if (e != hipSuccess) return e;
   // step 3: inverse transform (L^{-1}, or L^T for the adjoint) with the epilogue
   const int go = adjoint ? 3 : 1;

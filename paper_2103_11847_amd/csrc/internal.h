@@ -601,6 +601,8 @@ struct dctk_op_s {
   void* Ah;       // p*n1*n2, gemm dtype
   void* AhT;      // p*n2*n1: slices of Ah transposed (FP32 and 16-bit gemm types), else null
   void* Bh;       // p*s*s, gemm dtype (two-sided)
+  float top[2];   // FP32: largest finite magnitude of A~, B~
+  int small[2];   // FP32: whether A~, B~ hold numbers other than 0 below 2^-110
   double* Gd;     // 4 matrices p*p (L, L^-1, L^-T, L^T), FP64 (null for a fast operator)
   float* Gf;      // same in FP32
   int fast;       // 1: tubes longer than kMaxTube, transformed in O(p log p) (power-of-two p)
@@ -748,11 +750,24 @@ hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p,
                             const float* src, float* y, void* x, const float* G1, bool xin, const Ctl& ctl,
                             int* nblocks_out);
 
+// What the FP32 slice GEMM on the BF16 matrix cores knows of its operator operand
+// (A~, or B~ of a right factor; the other one is data): the largest finite
+// magnitude, and whether an element other than 0 lies below 2^-110.
+struct OperandRange {
+  float top;
+  int small;
+  int right;  // the operator is the right operand
+};
+constexpr int kRangeBlocks = 512;
+constexpr unsigned kSplitLow = (127u - 110u) << 23;  // bits of 2^-110
+// per block the largest finite magnitude's bits and the least one's above 0, minus 1, of n FP32 numbers
+hipError_t launch_range(dctk_ctx ctx, int64_t n, const float* in, unsigned* out);
+
 // C_k = op(A_k) op(B_k), batched over `batch`; tile 0: by problem size, else 32/64/128
 hipError_t launch_gemm(dctk_ctx ctx, hipStream_t s, int in_dtype, int out_acc, int M, int N, int K,
                        const void* A, int64_t lda, int64_t sA, int ta,
                        const void* B, int64_t ldb, int64_t sB, int tb,
-                       void* C, int64_t ldc, int64_t sC, int batch, Gate g, int tile = 0);
+                       void* C, int64_t ldc, int64_t sC, int batch, Gate g, int tile, const OperandRange& range);
 
 // Whether an operator can take the fused product, and whether it does in a direction.
 bool fused_eligible(dctk_op op);

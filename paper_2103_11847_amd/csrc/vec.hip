@@ -719,6 +719,33 @@ __global__ __launch_bounds__(kThreads) void k_cast(int64_t n, const double* in, 
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) out[e] = cvt<TO, double>(in[e]);
 }
 
+__global__ __launch_bounds__(kThreads) void k_range(int64_t n, const float* in, unsigned* out) {
+  __shared__ unsigned sh[2][kThreads / 64];
+  unsigned hi = 0, lo = ~0u;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
+    const unsigned m = __builtin_bit_cast(unsigned, in[e]) & 0x7fffffffu;
+    hi = m < 0x7f800000u ? max(hi, m) : hi;
+    lo = min(lo, m - 1u);
+  }
+  for (int d = 32; d > 0; d >>= 1) {
+    hi = max(hi, (unsigned)__shfl_xor((int)hi, d));
+    lo = min(lo, (unsigned)__shfl_xor((int)lo, d));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    sh[0][threadIdx.x >> 6] = hi;
+    sh[1][threadIdx.x >> 6] = lo;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int w = 1; w < kThreads / 64; ++w) {
+    hi = max(hi, sh[0][w]);
+    lo = min(lo, sh[1][w]);
+  }
+  out[2 * blockIdx.x] = hi;
+  out[2 * blockIdx.x + 1] = lo;
+}
+
 // out[k][c][r] = in[k][r][c] for p slices of rows x cols (operator setup only)
 template <typename TO>
 __global__ __launch_bounds__(kThreads) void k_cast_t(int64_t p, int64_t rows, int64_t cols, const double* in, TO* out) {
@@ -1042,6 +1069,12 @@ hipError_t launch_cast(dctk_ctx ctx, int64_t n, const double* in, int out_dtype,
     case DCTK_F16: hipLaunchKernelGGL(k_cast<f16_t>, dim3(grid), dim3(kThreads), 0, ctx->stream, n, in, (f16_t*)out); break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_range(dctk_ctx ctx, int64_t n, const float* in, unsigned* out) {
+  if (recording(ctx)) return hipErrorNotSupported;
+  hipLaunchKernelGGL(k_range, dim3(kRangeBlocks), dim3(kThreads), 0, ctx->stream, n, in, out);
   return hipGetLastError();
 }
 
