@@ -438,10 +438,11 @@ int dctk_lsqr_learned_solve(dctk_ctx ctx, dctk_krylov ws, dctk_mlp mlp, const vo
  * instance; the resulting schedule (one launch per kernel variant per
  * schedule point) is captured once into HIP graphs, one for each of up to three
  * classes of instances whose products launch different kernels; the graphs run
- * beside each other, the first on ctx's stream, the others on two streams that
- * the plans of a device share, between what ctx's stream held before the run
- * and what it is given after it.  (A stream under capture takes the launches
- * themselves, in order.)  Every instance computes exactly what its own
+ * beside each other, the first on ctx's stream, the others on two streams of the
+ * library, between what ctx's stream held before the run and what it is given
+ * after it; while those two streams hold an unfinished run of another caller's
+ * stream, one after the other on ctx's stream.  (A stream under capture takes the
+ * launches themselves, in order.)  Every instance computes exactly what its own
  * dctk_lsqr_tik_solve would.
  *
  * dctk_batch_create: count in [1, DCTK_BATCH_MAX]; ws[i] DCTK_KRYLOV_GKB

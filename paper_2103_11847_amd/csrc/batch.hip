@@ -39,17 +39,11 @@ struct dctk_batch_s {
   int chains;  // groups of instances whose launches are merged and replayed apart from the others'
   int single_launches;
   unsigned char* dev;  // argument arrays and workgroup maps of the merged launches
-  // per chain: its graph; for chains after the first also the stream it runs
-  // on (one of the device's side streams) and the event that the caller's
-  // stream waits for
   struct Chain {
     hipGraph_t graph;
     hipGraphExec_t exec;
-    hipStream_t stream;
-    hipEvent_t done;
   };
   std::vector<Chain> run;
-  hipEvent_t fork;
   bool side;   // holds a reference to the device's side streams
 };
 
@@ -57,44 +51,75 @@ namespace dctk {
 
 static const size_t kNone = (size_t)-1;
 
-// Streams for the chains after the first, shared by all plans of a device: a
-// process has few hardware queues (4), and streams created per plan come to
-// share the queue of the caller's stream or each other's, which runs the
-// chains one after the other (2.57 ms instead of 2.30 in the case at chain_of).
-// Shared by plans, they only order more than needed.  Created with a device's
-// first plan of several chains, destroyed with its last.
+// Streams for the chains after the first, one pair per device: a process has few
+// hardware queues (4), and streams created per plan come to share the queue of
+// the caller's stream or each other's, which runs the chains one after the
+// other (every other plan 2.50 ms instead of 2.04 in the case at chain_of).
+// One run at a time has them: a run from another stream, while the last one's
+// work is unfinished, would wait for that stream's caller, so it keeps to its
+// own stream (side_free).  Created with a device's first plan of several
+// chains, destroyed with its last.
 constexpr int kSideStreams = 2;
+constexpr int kSideDevices = 64;   // plans of devices beyond keep to the caller's stream
 struct Side {
+  std::mutex mutex;
   int refs = 0;
+  int last = 0;               // chains that the last run put on them
+  hipStream_t caller = nullptr;   // the stream that it was joined to
+  hipEvent_t fork = nullptr, done[kSideStreams] = {};
   hipStream_t s[kSideStreams] = {};
 };
-static std::mutex g_side_mutex;
-static std::map<int, Side> g_side;   // by device
+static Side g_side[kSideDevices];
 
-static hipError_t side_acquire(int device, hipStream_t* out) {
-  std::lock_guard<std::mutex> lock(g_side_mutex);
-  Side& d = g_side[device];
-  if (d.refs == 0)
-    for (int i = 0; i < kSideStreams; ++i) {
-      const hipError_t e = hipStreamCreateWithFlags(&d.s[i], hipStreamNonBlocking);
-      if (e != hipSuccess) {
-        while (i-- > 0) (void)hipStreamDestroy(d.s[i]);
-        return e;
-      }
+static void side_destroy(Side& d) {
+  for (int i = 0; i < kSideStreams; ++i) {
+    if (d.s[i]) {
+      (void)hipStreamSynchronize(d.s[i]);
+      (void)hipStreamDestroy(d.s[i]);
     }
+    if (d.done[i]) (void)hipEventDestroy(d.done[i]);
+    d.s[i] = nullptr;
+    d.done[i] = nullptr;
+  }
+  if (d.fork) (void)hipEventDestroy(d.fork);
+  d.fork = nullptr;
+  d.last = 0;
+}
+
+static hipError_t side_acquire(int device) {
+  Side& d = g_side[device];
+  std::lock_guard<std::mutex> lock(d.mutex);
+  if (d.refs == 0) {
+    hipError_t e = hipEventCreateWithFlags(&d.fork, hipEventDisableTiming);
+    for (int i = 0; i < kSideStreams && e == hipSuccess; ++i) {
+      e = hipStreamCreateWithFlags(&d.s[i], hipStreamNonBlocking);
+      if (e == hipSuccess) e = hipEventCreateWithFlags(&d.done[i], hipEventDisableTiming);
+    }
+    if (e != hipSuccess) {
+      side_destroy(d);
+      return e;
+    }
+  }
   d.refs += 1;
-  for (int i = 0; i < kSideStreams; ++i) out[i] = d.s[i];
   return hipSuccess;
 }
 
 static void side_release(int device) {
-  std::lock_guard<std::mutex> lock(g_side_mutex);
   Side& d = g_side[device];
-  if (--d.refs > 0) return;
-  for (int i = 0; i < kSideStreams; ++i) {
-    (void)hipStreamSynchronize(d.s[i]);
-    (void)hipStreamDestroy(d.s[i]);
-  }
+  std::lock_guard<std::mutex> lock(d.mutex);
+  if (--d.refs == 0) side_destroy(d);
+}
+
+// Whether a run from `caller` may have the side streams: the last run on them
+// is done, or was joined to the same stream, which orders the two anyway.
+static bool side_free(const Side& d, hipStream_t caller) {
+  if (d.last == 0 || d.caller == caller) return true;
+  for (int i = 0; i < d.last; ++i)
+    if (hipEventQuery(d.done[i]) != hipSuccess) {
+      (void)hipGetLastError();   // "not ready" is no error of a later launch
+      return false;
+    }
+  return true;
 }
 
 static hipError_t replay(dctk_batch b, hipStream_t s, int chain) {
@@ -111,15 +136,43 @@ static hipError_t replay(dctk_batch b, hipStream_t s, int chain) {
 
 static void batch_free(dctk_batch b) {
   for (auto& c : b->run) {
-    if (c.stream) (void)hipStreamSynchronize(c.stream);
     if (c.exec) (void)hipGraphExecDestroy(c.exec);
     if (c.graph) (void)hipGraphDestroy(c.graph);
-    if (c.done) (void)hipEventDestroy(c.done);
   }
-  if (b->fork) (void)hipEventDestroy(b->fork);
   if (b->side) side_release(b->ctx->device);
   if (b->dev) (void)hipFree(b->dev);
   delete b;
+}
+
+// The plan's graphs between what `caller` holds and what it is given next: the
+// first on that stream, the others on the side streams, or all of them on that
+// stream one after the other.
+static hipError_t run_chains(dctk_batch b, hipStream_t caller) {
+  const int n = (int)b->run.size();
+  if (b->side) {
+    Side& d = g_side[b->ctx->device];
+    std::unique_lock<std::mutex> lock(d.mutex, std::try_to_lock);
+    if (lock.owns_lock() && side_free(d, caller)) {
+      hipError_t e = hipEventRecord(d.fork, caller);
+      if (e != hipSuccess) return e;
+      d.last = n - 1;
+      d.caller = caller;
+      for (int c = 1; c < n; ++c) {
+        if ((e = hipStreamWaitEvent(d.s[c - 1], d.fork, 0)) != hipSuccess) return e;
+        if ((e = hipGraphLaunch(b->run[(size_t)c].exec, d.s[c - 1])) != hipSuccess) return e;
+        if ((e = hipEventRecord(d.done[c - 1], d.s[c - 1])) != hipSuccess) return e;
+      }
+      if ((e = hipGraphLaunch(b->run[0].exec, caller)) != hipSuccess) return e;
+      for (int c = 1; c < n; ++c)
+        if ((e = hipStreamWaitEvent(caller, d.done[c - 1], 0)) != hipSuccess) return e;
+      return hipSuccess;
+    }
+  }
+  for (int c = 0; c < n; ++c) {
+    const hipError_t e = hipGraphLaunch(b->run[(size_t)c].exec, caller);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -148,7 +201,6 @@ static hipError_t capture_chain(dctk_batch b, int chain) {
   }
   if (e == hipSuccess) e = hipGraphInstantiate(&c.exec, c.graph, nullptr, nullptr, 0);
   if (cs) (void)hipStreamDestroy(cs);
-  if (e == hipSuccess && chain > 0) e = hipEventCreateWithFlags(&c.done, hipEventDisableTiming);
   return e;
 }
 
@@ -229,7 +281,6 @@ int dctk_batch_create(dctk_ctx ctx, int count, const dctk_krylov* ws, const void
   b->single_launches = single;
   b->dev = nullptr;
   b->chains = chains;
-  b->fork = nullptr;
   b->side = false;
 
   // 3. lay out the argument arrays and workgroup maps of merged launches
@@ -288,15 +339,12 @@ int dctk_batch_create(dctk_ctx ctx, int count, const dctk_krylov* ws, const void
 
   // 4. capture every chain's schedule once
   if (use_graph) {
-    b->run.assign((size_t)chains, dctk_batch_s::Chain{nullptr, nullptr, nullptr, nullptr});
+    b->run.assign((size_t)chains, dctk_batch_s::Chain{nullptr, nullptr});
     hipError_t e = hipSuccess;
-    if (chains > 1) {
-      static_assert(kSideStreams == 2, "one per chain after the first");
-      hipStream_t side[kSideStreams];
-      e = side_acquire(ctx->device, side);
+    static_assert(kSideStreams == 2, "one per chain after the first");
+    if (chains > 1 && ctx->device < kSideDevices) {
+      e = side_acquire(ctx->device);
       b->side = e == hipSuccess;
-      for (int c = 1; c < chains && b->side; ++c) b->run[(size_t)c].stream = side[c - 1];
-      if (e == hipSuccess) e = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming);
     }
     for (int c = 0; c < chains && e == hipSuccess; ++c) e = capture_chain(b, c);
     if (e != hipSuccess) {
@@ -317,16 +365,7 @@ int dctk_batch_run(dctk_ctx ctx, dctk_batch b) {
   if (b->run.empty() || cap == hipStreamCaptureStatusActive) {
     DCTK_HIP(ctx, replay(b, ctx->stream, -1));
   } else {
-    // the first chain on the caller's stream, the others on their own between
-    // what the caller enqueued before and what it enqueues next
-    if (b->chains > 1) DCTK_HIP(ctx, hipEventRecord(b->fork, ctx->stream));
-    for (size_t c = 1; c < b->run.size(); ++c) {
-      DCTK_HIP(ctx, hipStreamWaitEvent(b->run[c].stream, b->fork, 0));
-      DCTK_HIP(ctx, hipGraphLaunch(b->run[c].exec, b->run[c].stream));
-      DCTK_HIP(ctx, hipEventRecord(b->run[c].done, b->run[c].stream));
-    }
-    DCTK_HIP(ctx, hipGraphLaunch(b->run[0].exec, ctx->stream));
-    for (size_t c = 1; c < b->run.size(); ++c) DCTK_HIP(ctx, hipStreamWaitEvent(ctx->stream, b->run[c].done, 0));
+    DCTK_HIP(ctx, run_chains(b, ctx->stream));
   }
   for (dctk_krylov w : b->ws) {
     w->host_steps = b->opts.k_max;
