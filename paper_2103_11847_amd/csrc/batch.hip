@@ -154,18 +154,27 @@ static hipError_t run_chains(dctk_batch b, hipStream_t caller) {
     std::unique_lock<std::mutex> lock(d.mutex, std::try_to_lock);
     if (lock.owns_lock() && side_free(d, caller)) {
       hipError_t e = hipEventRecord(d.fork, caller);
-      if (e != hipSuccess) return e;
       d.last = n - 1;
       d.caller = caller;
-      for (int c = 1; c < n; ++c) {
-        if ((e = hipStreamWaitEvent(d.s[c - 1], d.fork, 0)) != hipSuccess) return e;
-        if ((e = hipGraphLaunch(b->run[(size_t)c].exec, d.s[c - 1])) != hipSuccess) return e;
-        if ((e = hipEventRecord(d.done[c - 1], d.s[c - 1])) != hipSuccess) return e;
+      // A chain that is launched is joined, whatever fails after it: by the
+      // caller's stream, or here if that cannot be arranged.
+      int up = 1;   // chains [1, up) are launched
+      hipError_t joined[kSideStreams];
+      for (; up < n && e == hipSuccess; ++up) {
+        hipStream_t s = d.s[up - 1];
+        e = hipStreamWaitEvent(s, d.fork, 0);
+        if (e == hipSuccess) e = hipGraphLaunch(b->run[(size_t)up].exec, s);
+        if (e != hipSuccess) break;
+        joined[up - 1] = e = hipEventRecord(d.done[up - 1], s);
       }
-      if ((e = hipGraphLaunch(b->run[0].exec, caller)) != hipSuccess) return e;
-      for (int c = 1; c < n; ++c)
-        if ((e = hipStreamWaitEvent(caller, d.done[c - 1], 0)) != hipSuccess) return e;
-      return hipSuccess;
+      if (e == hipSuccess) e = hipGraphLaunch(b->run[0].exec, caller);
+      for (int c = 1; c < up; ++c) {
+        hipError_t j = joined[c - 1];
+        if (j == hipSuccess) j = hipStreamWaitEvent(caller, d.done[c - 1], 0);
+        if (j != hipSuccess) (void)hipStreamSynchronize(d.s[c - 1]);
+        if (e == hipSuccess) e = j;
+      }
+      return e;
     }
   }
   for (int c = 0; c < n; ++c) {

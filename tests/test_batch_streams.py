@@ -1,5 +1,5 @@
 """How a batch's chains of launches are ordered, on the CPU against a HIP runtime that logs the calls: no run waits
-for another caller's."""
+for another caller's, and no chain that was launched is left behind when a later call of the same run fails."""
 import ctypes
 import os
 import shutil
@@ -109,6 +109,32 @@ p.close()
 print("done")
 """
 
+JOIN = CHILD + r"""
+name, nth = sys.argv[2], int(sys.argv[3])
+c = context(0x100)
+p = Plan(c)
+stub.stub_fail(name.encode(), nth)
+r, calls = p.run()
+assert r == dk.DCTK_EHIP, r
+assert sum(bad for _, _, _, bad in calls) == 1
+for i, (n, s, _, bad) in enumerate(calls):
+    if n != "launch" or bad or s == 0x100:
+        continue
+    rest = calls[i + 1:]
+    synced = any(m == "sync" and t == s for m, t, _, _ in rest)
+    joined = any(m == "record" and t == s and not b2 and
+                 any(m2 == "wait" and t2 == 0x100 and e2 == e and not b3 for m2, t2, e2, b3 in rest[k + 1:])
+                 for k, (m, t, e, b2) in enumerate(rest))
+    assert synced or joined, (hex(s), calls)
+stub.stub_fail(b"", 0)
+r, calls = p.run()          # the plan is whole
+ok(r)
+assert len(launched(calls)) == 3
+p.close()
+print("done")
+"""
+
+
 @pytest.fixture(scope="module")
 def stub(tmp_path_factory):
     if not shutil.which("g++"):
@@ -125,3 +151,9 @@ def child(code, *args):
 
 def test_no_run_waits_for_another_stream(stub):
     child(STREAMS, stub)
+
+
+@pytest.mark.parametrize("name,nth", [("launch", i) for i in (1, 2, 3)] + [("record", i) for i in (1, 2, 3)] +
+                         [("wait", i) for i in (1, 2, 3, 4)])
+def test_failed_run_joins_its_chains(stub, name, nth):
+    child(JOIN, stub, name, str(nth))
