@@ -106,3 +106,17 @@ def test_largest_tile(ctx):
     A, X = rng.standard_normal((64, 510, 40)) * 2.0 ** -120, f32(rng.standard_normal((64, 40, 509)) * 2.0 ** 90)
     Y, ref = product(ctx, A, None, X, 0, False), Operator(A).apply(X)
     assert np.linalg.norm(Y - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("small", [False, True])
+def test_largest_tile_both_contiguous_in_k(ctx, small):
+    """The right factor of a two-sided adjoint with 64 slices of 500 x 509 outputs: 256 x 256 tiles, ragged both ways."""
+    from oracle.cprod import Operator
+    rng = np.random.default_rng(6)
+    A, B = rng.standard_normal((64, 24, 500)), rng.standard_normal((64, 509, 509))
+    R = f32(rng.standard_normal((64, 24, 509)))
+    if small:
+        A, R = A * 2.0 ** -60, f32(R * 2.0 ** -58)   # the intermediate loses bits, B brings the results back
+        B = B * 2.0 ** 90
+    Z, ref = product(ctx, A, B, R, 0, True), Operator(A, B).adjoint(R)
+    assert np.linalg.norm(Z - ref) <= 1e-5 * np.linalg.norm(ref)
