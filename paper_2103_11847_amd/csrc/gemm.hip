@@ -469,7 +469,7 @@ __global__ __launch_bounds__(256, 4) void gemm_ring_kernel(GemmArgs ga_, const G
 // registers while the current one is multiplied.  Out-of-range elements are
 // loaded from a clamped address and replaced by zero (no branches per load).
 template <typename T, int BM, int BN, int BK, bool TA, bool TB, int VW>
-__device__ __forceinline__ void gemm_mn_kernel_body(const GemmArgs& ga, const VBlock vb, const bool grouped) {
+__device__ __forceinline__ void gemm_mn_kernel_body(const GemmArgs& ga, const VBlock vb) {
   typedef Mfma<T> MF;
   typedef typename MF::frag_t frag_t;
   constexpr int KSTEP = MF::KSTEP;
@@ -606,12 +606,12 @@ __global__ __launch_bounds__(256) void gemm_mn_kernel(GemmArgs ga_, const GemmAr
   if constexpr (!GROUPED) {
     VBlock vb = hw_block();
     if (!slice_block(ga_, vb)) return;
-    gemm_mn_kernel_body<T, BM, BN, BK, TA, TB, VW>(ga_, vb, false);
+    gemm_mn_kernel_body<T, BM, BN, BK, TA, TB, VW>(ga_, vb);
   } else {
     VBlock vb;
     const GemmArgs g = group_args(grp, bmap, vb);
     if (!slice_block(g, vb)) return;   // the instance's grid may be padded
-    gemm_mn_kernel_body<T, BM, BN, BK, TA, TB, VW>(g, vb, true);
+    gemm_mn_kernel_body<T, BM, BN, BK, TA, TB, VW>(g, vb);
   }
 }
 
@@ -1011,10 +1011,12 @@ static hipError_t launch_gemm_mn(dctk_ctx ctx, hipStream_t s, GemmArgs ga, int t
     if (vec) DCTK_GMN(TA_, TB_, VW); \
     DCTK_GMN(TA_, TB_, 1);      \
   } while (0)
-  if (!ta && !tb) DCTK_GMN_V(false, false);
-  if (ta && !tb) DCTK_GMN_V(true, false);
-  if (!ta && tb) DCTK_GMN_V(false, true);
-  DCTK_GMN_V(true, true);
+  if constexpr (sizeof(T) == 8) {   // FP32 operators keep A~ transposed
+    if (ta && !tb) DCTK_GMN_V(true, false);
+  }
+  if (ta) return hipErrorInvalidValue;
+  if (!tb) DCTK_GMN_V(false, false);
+  DCTK_GMN_V(false, true);
 #undef DCTK_GMN_V
 #undef DCTK_GMN
 }
@@ -1031,10 +1033,8 @@ static hipError_t launch_gemm_split(dctk_ctx ctx, hipStream_t s, GemmArgs ga, in
 }
 
 // The split kernel's offsets within a tile are 32-bit (256 rows of lda, or 32
-// of ldb, floats), and its A~ has the contraction index contiguous.
-static bool split_shape_ok(int ta, int64_t lda, int64_t ldb) {
-  return !ta && lda < (1 << 20) && ldb < (1 << 20);
-}
+// of ldb, floats).
+static bool split_shape_ok(int64_t lda, int64_t ldb) { return lda < (1 << 20) && ldb < (1 << 20); }
 
 // Output tile edge of the split kernel: 256, 128 or 64, the one of least
 // estimated time per 32-long chunk, from what a tile of each takes while the
@@ -1083,7 +1083,7 @@ static hipError_t launch_gemm_vec(dctk_ctx ctx, hipStream_t s, int M, int N, int
   const int64_t t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * batch;
   constexpr int BK = sizeof(T) == 8 ? 16 : 32;
   if constexpr (sizeof(T) == 4) {
-    if (split_shape_ok(ta, lda, ldb)) {
+    if (split_shape_ok(lda, ldb)) {
       const int best = split_tile(M, N, batch, num_cus);
       if ((tile == 128 || (tile == 0 && t64 >= (int64_t)num_cus)) && best == 256)
         return launch_gemm_split<256, 256, 512, 2, 4>(ctx, s, ga, tb, batch);
@@ -1227,7 +1227,7 @@ static hipError_t slice_gemms(dctk_op op, hipStream_t s, int adjoint, const Ctl&
   hipError_t e;
   prof_begin(ctx, PROF_GEMM);
   // the left operand: A~ (n1 x n2), or for the adjoint A~^T (n2 x n1) -- read
-  // from the transposed copy when the operator keeps one (16-bit types)
+  // from the transposed copy that all but FP64 operators keep
   const bool tcopy = adjoint && op->AhT != nullptr;
   const void* Aop = tcopy ? op->AhT : op->Ah;
   const int64_t ldA = tcopy ? n1 : n2;

@@ -159,7 +159,7 @@ struct TubeArgs {
 };
 
 template <typename TIN, typename TOUT, typename TC, int KB, bool SCALE, bool EPI>
-__device__ __forceinline__ void tube_kernel_body(const TubeArgs& ta, const VBlock vb, const bool grouped) {
+__device__ __forceinline__ void tube_kernel_body(const TubeArgs& ta, const VBlock vb) {
   __shared__ double sh[kShCtl];
   const int p = ta.p;
   const int64_t count = ta.count;
@@ -258,11 +258,11 @@ __device__ __forceinline__ void tube_kernel_body(const TubeArgs& ta, const VBloc
 template <typename TIN, typename TOUT, typename TC, int KB, bool SCALE, bool EPI, bool GROUPED>
 __global__ __launch_bounds__(kThreads) void tube_kernel(TubeArgs ta_, const TubeArgs* grp, const int4* bmap) {
   if constexpr (!GROUPED) {
-    tube_kernel_body<TIN, TOUT, TC, KB, SCALE, EPI>(ta_, hw_block(), false);
+    tube_kernel_body<TIN, TOUT, TC, KB, SCALE, EPI>(ta_, hw_block());
   } else {
     VBlock vb;
     const TubeArgs g = group_args(grp, bmap, vb);
-    tube_kernel_body<TIN, TOUT, TC, KB, SCALE, EPI>(g, vb, true);
+    tube_kernel_body<TIN, TOUT, TC, KB, SCALE, EPI>(g, vb);
   }
 }
 
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kThreads) void tube_kernel(TubeArgs ta_, const Tube
 // waited for where they were masked, before the passes): 512 x 512 x 64 forward to FP32 36 -> 32.5 us,
 // to BF16 39.5 -> 33..
 template <typename T, typename TOUT, int PM, bool SCALE, bool EPI, bool VEC>
-__device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const VBlock vb, const bool grouped) {
+__device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const VBlock vb) {
   typedef Mfma<T> MF;
   constexpr int NB = 64;            // positions per tile
   // G as [k][t], t contiguous (+16 bytes; FP64 +32, two rows' operands per 64 bytes),
@@ -457,11 +457,11 @@ __device__ __forceinline__ void tube_mfma_kernel_body(const TubeArgs& ta, const 
 template <typename T, typename TOUT, int PM, bool SCALE, bool EPI, bool VEC, bool GROUPED>
 __global__ __launch_bounds__(256, sizeof(T) == 8 ? 2 : 4) void tube_mfma_kernel(TubeArgs ta_, const TubeArgs* grp, const int4* bmap) {
   if constexpr (!GROUPED) {
-    tube_mfma_kernel_body<T, TOUT, PM, SCALE, EPI, VEC>(ta_, hw_block(), false);
+    tube_mfma_kernel_body<T, TOUT, PM, SCALE, EPI, VEC>(ta_, hw_block());
   } else {
     VBlock vb;
     const TubeArgs g = group_args(grp, bmap, vb);
-    tube_mfma_kernel_body<T, TOUT, PM, SCALE, EPI, VEC>(g, vb, true);
+    tube_mfma_kernel_body<T, TOUT, PM, SCALE, EPI, VEC>(g, vb);
   }
 }
 
@@ -550,7 +550,7 @@ __device__ inline int pair_exp(double alpha1) {
 __device__ inline float pow2f(int e) { return __builtin_bit_cast(float, (127 + e) << 23); }
 
 template <typename TX, int PM, bool VEC>
-__device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const VBlock vb, const bool grouped) {
+__device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const VBlock vb) {
   typedef Mfma<float> MF;
   constexpr int NB = 64;
   // rows of G1 padded by 8: both the row reads of the first pass and the
@@ -725,7 +725,7 @@ __device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const 
 // and src in flight together (16 rows of 16 bytes per thread at p = 8).  Bound
 // by memory (16 B/element at 4 p flops); inside a Golub-Kahan step it replaces
 // the inverse and the forward transform's own launches and the re-read of y.
-template <typename TX, int KB>
+template <int KB>
 __device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const VBlock vb) {
   __shared__ float sG[KB * KB];
   __shared__ double sh[kShCtl];
@@ -764,7 +764,7 @@ __device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const V
   load(e0);
   double a_d, b_d, s_d;
   if (!ctl_eval(pa.ctl, cl, a_d, b_d, s_d, sh, vb)) return;
-  const int ex = std::is_same<TX, f16_t>::value ? 0 : pair_exp(alpha1);
+  const int ex = pair_exp(alpha1);
   const float xs = pow2f(-ex), b = has_src ? (float)b_d : 0.0f;
   const float a = (float)(a_d * s_d * (double)(pa.xin ? pow2f(ex) : 1.0f));
   const bool use_src = b != 0.0f;   // b = 0: src never enters
@@ -814,7 +814,7 @@ __device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const V
         }
 #pragma unroll
       for (int v = 0; v < 4; ++v) x[v] *= xs;
-      store_row((TX*)pa.x + (int64_t)k * count, e0, count, x);
+      store_row((float*)pa.x + (int64_t)k * count, e0, count, x);
     }
   }
   if (pa.ctl.part_out != nullptr) {
@@ -823,25 +823,25 @@ __device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const V
   }
 }
 
-template <typename TX, int KB, bool GROUPED>
+template <int KB, bool GROUPED>
 __global__ __launch_bounds__(kThreads) void tube_pair_small_kernel(PairArgs pa_, const PairArgs* grp, const int4* bmap) {
   if constexpr (!GROUPED) {
-    tube_pair_small_body<TX, KB>(pa_, hw_block());
+    tube_pair_small_body<KB>(pa_, hw_block());
   } else {
     VBlock vb;
     const PairArgs g = group_args(grp, bmap, vb);
-    tube_pair_small_body<TX, KB>(g, vb);
+    tube_pair_small_body<KB>(g, vb);
   }
 }
 
 template <typename TX, int PM, bool VEC, bool GROUPED>
 __global__ __launch_bounds__(256, 4) void tube_pair_kernel(PairArgs pa_, const PairArgs* grp, const int4* bmap) {
   if constexpr (!GROUPED) {
-    tube_pair_kernel_body<TX, PM, VEC>(pa_, hw_block(), false);
+    tube_pair_kernel_body<TX, PM, VEC>(pa_, hw_block());
   } else {
     VBlock vb;
     const PairArgs g = group_args(grp, bmap, vb);
-    tube_pair_kernel_body<TX, PM, VEC>(g, vb, true);
+    tube_pair_kernel_body<TX, PM, VEC>(g, vb);
   }
 }
 
@@ -876,17 +876,20 @@ hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p,
     if (vec) return launch_kernel(ctx, s, tube_pair_kernel<TX, PM_, true, false>, tube_pair_kernel<TX, PM_, true, true>, grid, 256, 0, pa); \
     return launch_kernel(ctx, s, tube_pair_kernel<TX, PM_, false, false>, tube_pair_kernel<TX, PM_, false, true>, grid, 256, 0, pa); \
   } while (0)
-#define DCTK_PAIR_S(TX, KB_) \
-  return launch_kernel(ctx, s, tube_pair_small_kernel<TX, KB_, false>, tube_pair_small_kernel<TX, KB_, true>, grid, kThreads, 0, pa)
+#define DCTK_PAIR_S(KB_) \
+  return launch_kernel(ctx, s, tube_pair_small_kernel<KB_, false>, tube_pair_small_kernel<KB_, true>, grid, kThreads, 0, pa)
 #define DCTK_PAIR_P(TX)            \
   do {                             \
-    if (p <= 4) DCTK_PAIR_S(TX, 4);   \
-    if (p <= 8) DCTK_PAIR_S(TX, 8);   \
     if (p <= 16) DCTK_PAIR_V(TX, 16); \
     if (p <= 32) DCTK_PAIR_V(TX, 32); \
     if (p <= 48) DCTK_PAIR_V(TX, 48); \
     DCTK_PAIR_V(TX, 64);           \
   } while (0)
+  if (small) {   // 16-bit products do not pair short tubes
+    if (x_dtype != DCTK_F32) return hipErrorInvalidValue;
+    if (p <= 4) DCTK_PAIR_S(4);
+    DCTK_PAIR_S(8);
+  }
   switch (x_dtype) {
     case DCTK_F32: DCTK_PAIR_P(float);
     case DCTK_BF16: DCTK_PAIR_P(bf16_t);

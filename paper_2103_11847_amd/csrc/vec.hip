@@ -551,14 +551,13 @@ struct ArnArgs {
 constexpr int kArnRows = 8;      // basis vectors per pass over w
 constexpr int kArnBlocks = 512;  // workgroups of k_arn_dots: two per CU, so k_arn_coef sums 512 partials per value
 
-template <typename T>
 __global__ __launch_bounds__(kThreads) void k_arn_dots(ArnArgs a) {
   if (!gate_open(a.g)) return;
   __shared__ double sh[kThreads / 64][2 * kArnRows];
-  const T* basis = (const T*)a.basis;
-  const T* w = (const T*)a.w;
+  const float* basis = (const float*)a.basis;
+  const float* w = (const float*)a.w;
   const int nb = a.nb, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const T* vj = basis + (int64_t)(nb - 1) * a.bstride;
+  const float* vj = basis + (int64_t)(nb - 1) * a.bstride;
   for (int i0 = 0; i0 < nb; i0 += kArnRows) {
     double aw[kArnRows], av[kArnRows];
 #pragma unroll
@@ -567,10 +566,10 @@ __global__ __launch_bounds__(kThreads) void k_arn_dots(ArnArgs a) {
       // all rows loaded before the first use; rows beyond the basis repeat the last one
       double bv[kArnRows][4], wv[4], jv[4];
       if (a.vec && e + 4 <= a.n) {
-        V4<T>::ld(w + e, wv);
-        V4<T>::ld(vj + e, jv);
+        V4<float>::ld(w + e, wv);
+        V4<float>::ld(vj + e, jv);
 #pragma unroll
-        for (int u = 0; u < kArnRows; ++u) V4<T>::ld(basis + (int64_t)min(i0 + u, nb - 1) * a.bstride + e, bv[u]);
+        for (int u = 0; u < kArnRows; ++u) V4<float>::ld(basis + (int64_t)min(i0 + u, nb - 1) * a.bstride + e, bv[u]);
       } else {
         ld4(w, e, a.n, false, wv);
         ld4(vj, e, a.n, false, jv);
@@ -642,13 +641,12 @@ __global__ __launch_bounds__(1024) void k_arn_coef(ArnArgs a) {
   }
 }
 
-template <typename T>
 __global__ __launch_bounds__(kThreads) void k_arn_sub(ArnArgs a) {
   if (!gate_open(a.g)) return;
   __shared__ double sh[kShCtl];
   __shared__ double sc[kMaxK];
-  const T* basis = (const T*)a.basis;
-  T* w = (T*)a.w;
+  const float* basis = (const float*)a.basis;
+  float* w = (float*)a.w;
   const int nb = a.nb;
   if ((int)threadIdx.x < nb) sc[threadIdx.x] = a.coef[threadIdx.x];
   __syncthreads();
@@ -661,7 +659,7 @@ __global__ __launch_bounds__(kThreads) void k_arn_sub(ArnArgs a) {
       double bv[kArnRows][4];
       if (vec) {
 #pragma unroll
-        for (int u = 0; u < kArnRows; ++u) V4<T>::ld(basis + (int64_t)min(i0 + u, nb - 1) * a.bstride + e, bv[u]);
+        for (int u = 0; u < kArnRows; ++u) V4<float>::ld(basis + (int64_t)min(i0 + u, nb - 1) * a.bstride + e, bv[u]);
       } else {
 #pragma unroll
         for (int u = 0; u < kArnRows; ++u) ld4(basis + (int64_t)min(i0 + u, nb - 1) * a.bstride, e, a.n, false, bv[u]);
@@ -677,7 +675,7 @@ __global__ __launch_bounds__(kThreads) void k_arn_sub(ArnArgs a) {
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      wv[q] = (double)(T)wv[q];
+      wv[q] = (double)(float)wv[q];
       acc += wv[q] * wv[q];
     }
     st4(w, e, a.n, vec, wv);
@@ -995,13 +993,13 @@ hipError_t launch_arn_mgs(dctk_ctx ctx, int dtype, int64_t n, void* w, const voi
   a.coef = coef;
   a.hcol = hcol;
   a.g = Gate{st, nb - 1, 1};  // runs when the product of the step ran
-  hipLaunchKernelGGL(k_arn_dots<float>, dim3(dots), dim3(kThreads), 0, ctx->stream, a);
+  hipLaunchKernelGGL(k_arn_dots, dim3(dots), dim3(kThreads), 0, ctx->stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_arn_coef, dim3(1), dim3(1024), 0, ctx->stream, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   a.part = part_out;
-  hipLaunchKernelGGL(k_arn_sub<float>, dim3(grid), dim3(kThreads), 0, ctx->stream, a);
+  hipLaunchKernelGGL(k_arn_sub, dim3(grid), dim3(kThreads), 0, ctx->stream, a);
   return hipGetLastError();
 }
 
