@@ -147,12 +147,13 @@ int dctk_tube_inv(dctk_ctx ctx, int tube, int adjoint_pair, int dtype, int64_t p
  * has run the work.  Rounding: FP32 results agree with the dense transform
  * to a relative 1e-6 (p = 256) to 4e-6 (p = 1024) in the 2-norm; the row
  * scaling D^{-1} (up to 2p / pi) amplifies the FFT's rounding by up to that
- * factor for the last rows of M and M^{-T}.  Blocks of E / p >= 2 tubes
- * (E = 4096 FP32, 2048 FP64) share complex FFTs in pairs: position e of a
- * block is the real part, e + E / (2p) the imaginary part, so a tube's error
- * is bounded relative to the norm of the pair's outputs (within 4x the
- * whole-array figures above), not its own: a tube next to a partner 1e4
- * times larger gets ~1e4 times its own relative error.
+ * factor for the last rows of M and M^{-T}.  Two tubes share a
+ * complex FFT as its real and imaginary parts: positions 2e and 2e + 1 for p
+ * from 128 to 1024, else, in blocks of E / p >= 2 tubes (E = 4096 FP32, 2048
+ * FP64), positions e and e + E / (2p) of a block.  So a tube's error is bounded
+ * relative to the norm of the pair's outputs (within 4x the whole-array figures
+ * above), not its own: a tube next to a partner 1e4 times larger gets ~1e4 times
+ * its own relative error.
  * Errors: DCTK_EINVAL (NULL, bad tube/which, in and out overlap),
  * DCTK_EDTYPE, DCTK_ESHAPE (p not allowed, count <= 0), DCTK_ESTATE (while a
  * batch plan is being recorded), DCTK_EHIP. */
@@ -221,8 +222,9 @@ int dctk_op_destroy(dctk_op op);
  * operators with p <= 8) -- or as three kernels: tube transform, batched slice
  * GEMMs, inverse transform with epilogue (Algorithm 1 steps 1-3).  The
  * output tile edge of the GEMM part is 16, 32 or 64 (fused) or 32, 64, 128
- * or 256 (three kernels; 128 not for FP64; 256, tiles of 256 x 128, only for
- * BF16 and FP16 GEMMs).  All paths compute the same product;
+ * or 256 (three kernels; 128 not for FP64, and for FP32 the larger of 128 and
+ * 256 where that takes less time, with the same sums; 256, tiles of 256 x 128,
+ * only for BF16 and FP16 GEMMs).  All paths compute the same product;
  * results differ only by the rounding of the contraction order.
  * dctk_op_autotune: times every path and tile the operator can take, `reps`
  * launches each (1..1000) of the forward and of the adjoint product on ctx's

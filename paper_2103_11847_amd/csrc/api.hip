@@ -425,17 +425,19 @@ static int op_create_impl(dctk_ctx ctx, int tube, int gemm_dtype, int nd, const 
   const int64_t pp = p * p;
   std::vector<double> Gd;
   if (!fast) build_op_matrices(tube, nd, dims, p, Gd);
-  std::vector<float> Gf(Gd.size());
+  // FP32 matrices, then the OperandRange words, which the casts of A~ and B~ raise from 0
+  std::vector<float> Gf(Gd.size() + kRangeWords, 0.0f);
   for (size_t i = 0; i < Gd.size(); ++i) Gf[i] = (float)Gd[i];
   double* tmp = nullptr;
   hipError_t e = hipSetDevice(ctx->device);
 #define DCTK_TRY(call) do { if (e == hipSuccess) e = (call); } while (0)
   if (!fast) {
     DCTK_TRY(hipMalloc((void**)&op->Gd, sizeof(double) * 4 * pp));
-    DCTK_TRY(hipMalloc((void**)&op->Gf, sizeof(float) * 4 * pp));
     DCTK_TRY(hipMemcpy(op->Gd, Gd.data(), sizeof(double) * 4 * pp, hipMemcpyHostToDevice));
-    DCTK_TRY(hipMemcpy(op->Gf, Gf.data(), sizeof(float) * 4 * pp, hipMemcpyHostToDevice));
   }
+  DCTK_TRY(hipMalloc((void**)&op->Gf, sizeof(float) * Gf.size()));
+  DCTK_TRY(hipMemcpy(op->Gf, Gf.data(), sizeof(float) * Gf.size(), hipMemcpyHostToDevice));
+  if (gemm_dtype == DCTK_F32 && e == hipSuccess) op->range = (unsigned*)(op->Gf + Gd.size());
   DCTK_TRY(hipMalloc(&op->Ah, ge * (size_t)(p * n1 * n2)));
   // 16-bit products read A~ with the contraction index contiguous in both
   // directions (16-byte rows straight into LDS): keep the transposed slices
@@ -464,33 +466,15 @@ static int op_create_impl(dctk_ctx ctx, int tube, int gemm_dtype, int nd, const 
     if (op->two_sided) DCTK_TRY(DCTK_TUBE_F64(B, op->Bh, s * s));
   } else {
     DCTK_TRY(DCTK_TUBE_F64(A, tmp, n1 * n2));
-    DCTK_TRY(launch_cast(ctx, p * n1 * n2, tmp, gemm_dtype, op->Ah));
+    DCTK_TRY(launch_cast(ctx, p * n1 * n2, tmp, gemm_dtype, op->Ah, op->range));
     if (op->AhT) DCTK_TRY(launch_cast_t(ctx, p, n1, n2, tmp, gemm_dtype, op->AhT));
     if (op->two_sided) {
       DCTK_TRY(DCTK_TUBE_F64(B, tmp, s * s));
-      DCTK_TRY(launch_cast(ctx, p * s * s, tmp, gemm_dtype, op->Bh));
+      DCTK_TRY(launch_cast(ctx, p * s * s, tmp, gemm_dtype, op->Bh, op->range ? op->range + 2 : nullptr));
     }
   }
 #undef DCTK_TUBE_F64
-  // the range of the FP32 operands (the slice GEMM's OperandRange)
-  static_assert(2 * 2 * kRangeBlocks * sizeof(unsigned) <= sizeof(double) * kRedBlocks, "fits the scratch");
-  unsigned range[2][kRangeBlocks][2];
-  const int ops = gemm_dtype == DCTK_F32 ? 1 + op->two_sided : 0;
-  for (int o = 0; o < ops; ++o) {
-    unsigned* dev = (unsigned*)ctx->red_partials + o * 2 * kRangeBlocks;
-    DCTK_TRY(launch_range(ctx, o ? p * s * s : p * n1 * n2, (const float*)(o ? op->Bh : op->Ah), dev));
-    DCTK_TRY(hipMemcpyAsync(range[o], dev, sizeof(range[o]), hipMemcpyDeviceToHost, ctx->stream));
-  }
   DCTK_TRY(hipStreamSynchronize(ctx->stream));
-  for (int o = 0; o < ops && e == hipSuccess; ++o) {
-    unsigned hi = 0, lo = ~0u;
-    for (int b = 0; b < kRangeBlocks; ++b) {
-      hi = std::max(hi, range[o][b][0]);
-      lo = std::min(lo, range[o][b][1]);
-    }
-    memcpy(&op->top[o], &hi, sizeof(float));
-    op->small[o] = lo < kSplitLow - 1u;
-  }
 #undef DCTK_TRY
   if (tmp) (void)hipFree(tmp);
   if (e != hipSuccess) {

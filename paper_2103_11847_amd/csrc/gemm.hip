@@ -640,9 +640,11 @@ __global__ __launch_bounds__(256) void gemm_mn_kernel(GemmArgs ga_, const GemmAr
 // What is read beyond K in a row of A~ (the next row's start) meets a zero row
 // of the right operand; with both operands contiguous in k (TB) the last chunk
 // of A~ is zeroed explicitly.
-// Bound: the matrix cores at the rate their power allows (64 x 512^3: 94 us =
-// 1.10 PFLOP/s of BF16, a large BF16 library product 1.19; FP32 instruction
-// 144 us; 3 x 1024^3: 49 us against 70; 32 x 256^3: 12.4 us against 16.3).
+// Bound: neither memory nor the matrix cores, which are busy 45 % of the time,
+// but what happens between a chunk's two barriers (the splitting's vector work and
+// the LDS traffic of three planes) and, with one tile per CU, the results leaving
+// at the end (13 us of 64 x 512^3).  Kernel times, FP32 instruction before -> now:
+// 64 x 512^3 139 -> 83 us, 3 x 1024^3 67 -> 46, 32 x 256^3 16.3 -> 12.4.
 //
 // The split does not represent infinities and NaN (their remainders are NaN),
 // values that round to infinity in bfloat16, nor all 24 bits of numbers below
@@ -656,8 +658,8 @@ __global__ __launch_bounds__(256) void gemm_mn_kernel(GemmArgs ga_, const GemmAr
 // step the data is of norm 1 and neither is needed.  No number is tested in the
 // loop (that cost 49 -> 54 us at 3 x 1024^3), and results that are merely small
 // cost nothing: the BF16 instruction keeps subnormal operands and results.
-// 64 x 512^3: 106 us, 126 where every tile looks at its data, 290 where
-// every tile is computed again; 3 x 1024^3: 49, 59 and 140 us.
+// Between events on random data, 64 x 512^3: 106 us, 126 where every tile looks
+// at its data, 290 where every tile is computed again; 3 x 1024^3: 49, 59 and 140.
 struct Split8 {
   uint4 h[3];
 };
@@ -703,12 +705,13 @@ __device__ inline unsigned split_reach(int K, float top) {
 // and numbers that lose bits (seen[3]), and if a result is within reach of
 // either's losses, the tile is computed again with the FP32 instruction,
 // operands staged as they are.  `least` is twice the bits of the least magnitude
-// among the lane's results.  Nothing of the split loop is taken over, the
-// arguments neither (they are read again through gp): what both would share
-// cost registers in the loop (14.7 -> 15.9 us at 31 x 243 x 211 x 197).
+// among the lane's results, `small` whether the operator holds such numbers.
+// Nothing of the split loop is taken over, the arguments neither (they are read
+// again through gp): what both would share cost registers in the loop (14.7 ->
+// 15.9 us at 31 x 243 x 211 x 197).
 template <int BM, int BN, int NT, int WGM, int WGN, bool TB>
-__device__ __forceinline__ void split_again(const GemmArgs* gp, int bx, int by, int bz, unsigned least, lds_float* As,
-                                            lds_float* Bs, lds_uint* seen) {
+__device__ __forceinline__ void split_again(const GemmArgs* gp, int bx, int by, int bz, unsigned least, unsigned small,
+                                            lds_float* As, lds_float* Bs, lds_uint* seen) {
   constexpr int BK = 32, LD = BK + 4;
   constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 16, FN = WN / 16;
   static_assert(LD <= 3 * BK / 2, "the rows fit the three planes");
@@ -764,7 +767,7 @@ __device__ __forceinline__ void split_again(const GemmArgs* gp, int bx, int by, 
     if (lane == 0) __hip_atomic_fetch_max(&seen[2], top >> 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (__any(low < 2u * kSplitLow - 1u)) seen[3] = 1;
     __syncthreads();
-    if (ga.range.small != 0 && __any(least < split_reach(K, __builtin_bit_cast(float, seen[2])))) seen[4] = 1;
+    if (small != 0 && __any(least < split_reach(K, __builtin_bit_cast(float, seen[2])))) seen[4] = 1;
     __syncthreads();
     if (seen[4] == 0 && (seen[1] == 0 || seen[3] == 0)) return;
   }
@@ -824,6 +827,14 @@ __device__ __forceinline__ void split_again(const GemmArgs* gp, int bx, int by, 
         if (row < M && col < N) C[(int64_t)row * ga.ldc + col] = acc[i][j][r];
       }
     }
+}
+
+// The same through a call, for tiles whose loop takes every register (inlined,
+// 256 x 256 spilled some of them: 3 MB a launch at 64 x 512^3).
+template <int BM, int BN, int NT, int WGM, int WGN, bool TB>
+static __device__ __attribute__((noinline)) void split_again_call(const GemmArgs* gp, int bx, int by, int bz, unsigned least,
+                                                                  unsigned small, lds_float* As, lds_float* Bs, lds_uint* seen) {
+  split_again<BM, BN, NT, WGM, WGN, TB>(gp, bx, by, bz, least, small, As, Bs, seen);
 }
 
 template <int BM, int BN, int NT, int WGM, int WGN, bool TB>
@@ -911,7 +922,12 @@ __device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
+  // the operator's range, or, where the data has norm 1 and the operators are not tiny, one that nothing reaches
+  const unsigned *rg = ga.range.at, both = ga.range.unit == 2 ? min(rg[0], rg[2]) : rg[0];
+  const unsigned top_ = rg[2 * ga.range.right], low_ = ~rg[2 * ga.range.right + 1];
   load_chunk(0);
+  const bool near = ga.range.unit != 0 && __builtin_amdgcn_readfirstlane(both) >= (127u - 40u) << 23;
+  const unsigned top = near ? 0u : __builtin_amdgcn_readfirstlane(top_), small = !near && (unsigned)__builtin_amdgcn_readfirstlane(low_) < kSplitLow - 1u;
   if (tid < kSplitSeen) seen[tid] = 0;
   for (int k0 = 0; k0 < K; k0 += BK) {
     __syncthreads();
@@ -965,7 +981,7 @@ __device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const
   if (m0 + BM <= M) look(std::false_type{});
   else look(std::true_type{});
   if (__any(most >= 0xff000000u)) seen[0] = 1;
-  if (__any(least < split_reach(K, ga.range.top))) seen[1] = 1;
+  if (__any(least < split_reach(K, __builtin_bit_cast(float, top)))) seen[1] = 1;
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < FM; ++i)
@@ -978,9 +994,11 @@ __device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const
         if (row < M && col < N) C[(int64_t)row * ga.ldc + col] = acc[i][j][r];
       }
     }
-  if ((seen[0] | seen[1]) != 0 || ga.range.small != 0)
-    split_again<BM, BN, NT, WGM, WGN, TB>(gp, vb.x, vb.y, vb.z, least, (lds_float*)&As[0][0], (lds_float*)&Bs[0][0],
-                                          (lds_uint*)seen);
+  if ((seen[0] | seen[1]) != 0 || small != 0) {
+    lds_float *la = (lds_float*)&As[0][0], *lb = (lds_float*)&Bs[0][0];
+    if constexpr (BM >= 256) split_again_call<BM, BN, NT, WGM, WGN, TB>(gp, vb.x, vb.y, vb.z, least, small, la, lb, (lds_uint*)seen);
+    else split_again<BM, BN, NT, WGM, WGN, TB>(gp, vb.x, vb.y, vb.z, least, small, la, lb, (lds_uint*)seen);
+  }
 }
 
 template <int BM, int BN, int NT, int WGM, int WGN, bool TB, bool GROUPED>
@@ -1213,9 +1231,10 @@ static Gate gemm_gate(const Ctl& ctl) {
 }
 
 // Step 2 of a three-kernel product: the slice products of X~ (op->xh) into op->ch.
-// In a Krylov step X~ is that of a vector of norm 1, or near it: what the FP32
-// operands lose below 2^-110 is then far below the product's rounding, unless
-// the operator itself is that small, and nothing has to be looked for.
+// In a Krylov step X~ is that of a vector of norm 1, or near it (OperandRange's
+// unit): what the FP32 operands lose below 2^-110 is then far below the product's
+// rounding, unless an operator itself is that small (the kernel sees to that),
+// and nothing has to be looked for.
 static hipError_t slice_gemms(dctk_op op, hipStream_t s, int adjoint, const Ctl& ctl) {
   dctk_ctx ctx = op->ctx;
   const int tile = op->tune[adjoint ? 1 : 0][1];
@@ -1233,9 +1252,8 @@ static hipError_t slice_gemms(dctk_op op, hipStream_t s, int adjoint, const Ctl&
   const int64_t ldA = tcopy ? n1 : n2;
   const int tA = adjoint && !tcopy ? 1 : 0;
   const Gate g = gemm_gate(ctl);
-  const bool unit = ctl.kind != CTL_PLAIN && op->top[0] >= 0x1p-40f && (!op->two_sided || op->top[1] >= 0x1p-40f);
-  const OperandRange ra = unit ? OperandRange{0.0f, 0, 0} : OperandRange{op->top[0], op->small[0], 0};
-  const OperandRange rb = unit ? OperandRange{0.0f, 0, 1} : OperandRange{op->top[1], op->small[1], 1};
+  const int unit = ctl.kind != CTL_PLAIN ? 1 + op->two_sided : 0;
+  const OperandRange ra{op->range, 0, unit}, rb{op->range, 1, unit};
   if (!op->two_sided) {
     // forward: (n1 x n2)(n2 x s);  adjoint: (n2 x n1 := A~^T)(n1 x s)
     e = launch_gemm(ctx, s, gdt, 1, (int)rout, (int)sc, (int)rin, Aop, ldA, sAh, tA,

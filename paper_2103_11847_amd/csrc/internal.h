@@ -601,10 +601,9 @@ struct dctk_op_s {
   void* Ah;       // p*n1*n2, gemm dtype
   void* AhT;      // p*n2*n1: slices of Ah transposed (FP32 and 16-bit gemm types), else null
   void* Bh;       // p*s*s, gemm dtype (two-sided)
-  float top[2];   // FP32: largest finite magnitude of A~, B~
-  int small[2];   // FP32: whether A~, B~ hold numbers other than 0 below 2^-110
   double* Gd;     // 4 matrices p*p (L, L^-1, L^-T, L^T), FP64 (null for a fast operator)
-  float* Gf;      // same in FP32
+  float* Gf;      // same in FP32, then the OperandRange words
+  unsigned* range;  // FP32: those words
   int fast;       // 1: tubes longer than kMaxTube, transformed in O(p log p) (power-of-two p)
   void* xh;       // transformed operand, gemm dtype, p*max(n1,n2)*s
   void* th;       // two-sided intermediate, gemm dtype, p*max(n1,n2)*s
@@ -751,17 +750,14 @@ hipError_t launch_tube_pair(dctk_ctx ctx, hipStream_t s, int x_dtype, int64_t p,
                             int* nblocks_out);
 
 // What the FP32 slice GEMM on the BF16 matrix cores knows of its operator operand
-// (A~, or B~ of a right factor; the other one is data): the largest finite
-// magnitude, and whether an element other than 0 lies below 2^-110.
+// (A~, or B~ of a right factor; the other one is data).
 struct OperandRange {
-  float top;
-  int small;
-  int right;  // the operator is the right operand
+  const unsigned* at;  // an operator's {A~, B~} x {largest finite magnitude's bits, ~(the least one's above 0, minus 1)}
+  int right;           // the operator is the right operand, B~
+  int unit;            // the data is, or comes from, a vector of norm about 1 (2: and the operator has a B~)
 };
-constexpr int kRangeBlocks = 512;
+constexpr int kRangeWords = 4;
 constexpr unsigned kSplitLow = (127u - 110u) << 23;  // bits of 2^-110
-// per block the largest finite magnitude's bits and the least one's above 0, minus 1, of n FP32 numbers
-hipError_t launch_range(dctk_ctx ctx, int64_t n, const float* in, unsigned* out);
 
 // C_k = op(A_k) op(B_k), batched over `batch`; tile 0: by problem size, else 32/64/128
 hipError_t launch_gemm(dctk_ctx ctx, hipStream_t s, int in_dtype, int out_acc, int M, int N, int K,
@@ -838,7 +834,8 @@ hipError_t launch_gkb_start(dctk_ctx ctx, int dtype, int64_t n, void* X, void* W
 hipError_t launch_gkb_update(dctk_ctx ctx, int dtype, int64_t n, void* X, void* W, const void* Vin, void* Vn,
                              const double* part, int npart, KState* st, int j, void* U = nullptr);
 hipError_t launch_state_reset(dctk_ctx ctx, KState* st, int full, double tol);
-hipError_t launch_cast(dctk_ctx ctx, int64_t n, const double* in, int out_dtype, void* out);
+// (range: FP32 results only, two words of an OperandRange, zeros before)
+hipError_t launch_cast(dctk_ctx ctx, int64_t n, const double* in, int out_dtype, void* out, unsigned* range);
 // Transposing cast of p slices rows x cols (FP64) to cols x rows (FP32 and 16-bit types).
 hipError_t launch_cast_t(dctk_ctx ctx, int64_t p, int64_t rows, int64_t cols, const double* in, int out_dtype,
                          void* out);

@@ -519,8 +519,8 @@ __global__ __launch_bounds__(kThreads) void k_arn_start(int64_t n, T* out, const
   }
 }
 
-// Modified Gram-Schmidt of Algorithm 2 step 3(b) for step j, in two passes over
-// the basis instead of one pass over w per basis vector.  MGS takes
+// Modified Gram-Schmidt of Algorithm 2 step 3(b) for step j of FP32 vectors (FP64
+// ones: k_mgs, below), in two passes over the basis instead of one pass over w per basis vector.  MGS takes
 //   h_i = <v_i, w - sum_{l < i} h_l v_l> = <v_i, w> - sum_{l < i} <v_i, v_l> h_l,
 // so with r_i = <v_i, w> and the strictly lower triangle L of the Gram matrix
 // of the basis its coefficients solve (I + L) h = r, whatever the loss of
@@ -717,31 +717,34 @@ __global__ __launch_bounds__(kThreads) void k_cast(int64_t n, const double* in, 
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) out[e] = cvt<TO, double>(in[e]);
 }
 
-__global__ __launch_bounds__(kThreads) void k_range(int64_t n, const float* in, unsigned* out) {
+// FP32, and the range of what it writes: one pair of atomics a workgroup, so few of
+// them (a pair for every 256 numbers took 100 us at 32 x 256 x 256)
+__global__ __launch_bounds__(kThreads) void k_cast_range(int64_t n, const double* in, float* out, unsigned* range) {
   __shared__ unsigned sh[2][kThreads / 64];
-  unsigned hi = 0, lo = ~0u;
+  unsigned hi = 0, lo = 0;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+#pragma unroll 4
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-    const unsigned m = __builtin_bit_cast(unsigned, in[e]) & 0x7fffffffu;
+    const float v = cvt<float, double>(in[e]);
+    const unsigned m = __builtin_bit_cast(unsigned, v) & 0x7fffffffu;
+    out[e] = v;
     hi = m < 0x7f800000u ? max(hi, m) : hi;
-    lo = min(lo, m - 1u);
+    lo = max(lo, ~(m - 1u));
   }
   for (int d = 32; d > 0; d >>= 1) {
     hi = max(hi, (unsigned)__shfl_xor((int)hi, d));
-    lo = min(lo, (unsigned)__shfl_xor((int)lo, d));
+    lo = max(lo, (unsigned)__shfl_xor((int)lo, d));
   }
   if ((threadIdx.x & 63) == 0) {
     sh[0][threadIdx.x >> 6] = hi;
     sh[1][threadIdx.x >> 6] = lo;
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  for (int w = 1; w < kThreads / 64; ++w) {
-    hi = max(hi, sh[0][w]);
-    lo = min(lo, sh[1][w]);
+  if (threadIdx.x < 2) {
+    unsigned m = 0;
+    for (int w = 0; w < kThreads / 64; ++w) m = max(m, sh[threadIdx.x][w]);
+    atomicMax(range + threadIdx.x, m);
   }
-  out[2 * blockIdx.x] = hi;
-  out[2 * blockIdx.x + 1] = lo;
 }
 
 // out[k][c][r] = in[k][r][c] for p slices of rows x cols (operator setup only)
@@ -1057,22 +1060,16 @@ hipError_t launch_gkb_update(dctk_ctx ctx, int dtype, int64_t n, void* X, void* 
   return launch_kernel(ctx, ctx->stream, k_gkb_update<float, false>, k_gkb_update<float, true>, dim3(grid), kThreads, 0, a);
 }
 
-hipError_t launch_cast(dctk_ctx ctx, int64_t n, const double* in, int out_dtype, void* out) {
+hipError_t launch_cast(dctk_ctx ctx, int64_t n, const double* in, int out_dtype, void* out, unsigned* range) {
   if (recording(ctx)) return hipErrorNotSupported;
   unsigned grid = grid_for(n * 4);
   switch (out_dtype) {
     case DCTK_F64: hipLaunchKernelGGL(k_cast<double>, dim3(grid), dim3(kThreads), 0, ctx->stream, n, in, (double*)out); break;
-    case DCTK_F32: hipLaunchKernelGGL(k_cast<float>, dim3(grid), dim3(kThreads), 0, ctx->stream, n, in, (float*)out); break;
+    case DCTK_F32: hipLaunchKernelGGL(k_cast_range, dim3(std::min(grid, 1024u)), dim3(kThreads), 0, ctx->stream, n, in, (float*)out, range); break;
     case DCTK_BF16: hipLaunchKernelGGL(k_cast<bf16_t>, dim3(grid), dim3(kThreads), 0, ctx->stream, n, in, (bf16_t*)out); break;
     case DCTK_F16: hipLaunchKernelGGL(k_cast<f16_t>, dim3(grid), dim3(kThreads), 0, ctx->stream, n, in, (f16_t*)out); break;
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_range(dctk_ctx ctx, int64_t n, const float* in, unsigned* out) {
-  if (recording(ctx)) return hipErrorNotSupported;
-  hipLaunchKernelGGL(k_range, dim3(kRangeBlocks), dim3(kThreads), 0, ctx->stream, n, in, out);
   return hipGetLastError();
 }
 
