@@ -31,8 +31,8 @@ struct GemmArgs {
   void* C;
   int64_t ldc, sC;
   Gate g;
-  OperandRange range;   // FP32
   int nbatch;   // > 0: slices placed per XCD (see slice_block); the grid's z is padded to 8 ceil(nbatch / 8)
+  OperandRange range;   // FP32, split kernel (last: in the middle it cost every small product 0.1 us of argument loads)
 };
 
 // XCD-aware slice placement of a plain batched launch.  Workgroups are dealt to
@@ -829,15 +829,17 @@ __device__ __forceinline__ void split_again(const GemmArgs* gp, int bx, int by, 
     }
 }
 
-// The same through a call, for tiles whose loop takes every register (inlined,
-// 256 x 256 spilled some of them: 3 MB a launch at 64 x 512^3).
+// The same through a call, for kernels whose loop takes every register (inlined,
+// 256 x 256 spilled some of them, 3 MB a launch at 64 x 512^3, and five workgroups
+// of 64 x 64 a CU lost 4 % to fewer registers in the loop); elsewhere the call's
+// scratch costs more (batches 0.7 %).
 template <int BM, int BN, int NT, int WGM, int WGN, bool TB>
 static __device__ __attribute__((noinline)) void split_again_call(const GemmArgs* gp, int bx, int by, int bz, unsigned least,
                                                                   unsigned small, lds_float* As, lds_float* Bs, lds_uint* seen) {
   split_again<BM, BN, NT, WGM, WGN, TB>(gp, bx, by, bz, least, small, As, Bs, seen);
 }
 
-template <int BM, int BN, int NT, int WGM, int WGN, bool TB>
+template <int BM, int BN, int NT, int WGM, int WGN, bool CALL, bool TB>
 __device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const GemmArgs* gp, const VBlock vb) {
   constexpr int BK = 32;
   constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 16, FN = WN / 16;
@@ -956,10 +958,10 @@ __device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const
     }
   }
 
-  // The least and the largest of twice the results' magnitudes in bits (rows
-  // beyond the operand are zeros; columns beyond it are the next row's data, and
-  // may stay).  Agreed on before the results leave: a barrier after the stores
-  // would wait for them.
+  // The least and the largest of twice the results' magnitudes in bits.  What lies
+  // beyond the operands is zeros, which do not count, but for columns beyond a B
+  // contiguous in n: those are the next row's data, and may stay.  Agreed on before
+  // the results leave: a barrier after the stores would wait for them.
   unsigned least = ~0u, most = 0;
   auto look = [&](auto edge_c) {
 #pragma unroll
@@ -971,14 +973,14 @@ __device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const
         for (int j = 0; j < FN; ++j) {
           const float v = acc[i][j][r];
           const unsigned t = __builtin_bit_cast(unsigned, v) << 1;
-          l = min(l, t);
+          l = min(l, !TB || !decltype(edge_c)::value || n0 + wn * WN + j * 16 + lr < N ? t : ~0u);
           most = max(most, t);
         }
         if (decltype(edge_c)::value) l = m0 + wm * WM + i * 16 + lg * 4 + r < M ? l : ~0u;
         least = min(least, l);
       }
   };
-  if (m0 + BM <= M) look(std::false_type{});
+  if (m0 + BM <= M && (!TB || n0 + BN <= N)) look(std::false_type{});
   else look(std::true_type{});
   if (__any(most >= 0xff000000u)) seen[0] = 1;
   if (__any(least < split_reach(K, __builtin_bit_cast(float, top)))) seen[1] = 1;
@@ -996,23 +998,24 @@ __device__ __forceinline__ void gemm_split_kernel_body(const GemmArgs& ga, const
     }
   if ((seen[0] | seen[1]) != 0 || small != 0) {
     lds_float *la = (lds_float*)&As[0][0], *lb = (lds_float*)&Bs[0][0];
-    if constexpr (BM >= 256) split_again_call<BM, BN, NT, WGM, WGN, TB>(gp, vb.x, vb.y, vb.z, least, small, la, lb, (lds_uint*)seen);
+    if constexpr (CALL) split_again_call<BM, BN, NT, WGM, WGN, TB>(gp, vb.x, vb.y, vb.z, least, small, la, lb, (lds_uint*)seen);
     else split_again<BM, BN, NT, WGM, WGN, TB>(gp, vb.x, vb.y, vb.z, least, small, la, lb, (lds_uint*)seen);
   }
 }
 
-template <int BM, int BN, int NT, int WGM, int WGN, bool TB, bool GROUPED>
-__global__ __launch_bounds__(NT, BM == 64 ? 4 : 2) void gemm_split_kernel(GemmArgs ga_, const GemmArgs* grp, const int4* bmap) {
+template <int BM, int BN, int NT, int WGM, int WGN, int WAVES, bool TB, bool GROUPED>
+__global__ __launch_bounds__(NT, WAVES) void gemm_split_kernel(GemmArgs ga_, const GemmArgs* grp, const int4* bmap) {
+  constexpr bool CALL = BM >= 256 || WAVES > 4;   // no registers to spare
   if constexpr (!GROUPED) {
     VBlock vb = hw_block();
     if (!slice_block(ga_, vb)) return;
     // (the arguments where the kernel finds them: the first one, from the segment's start)
-    gemm_split_kernel_body<BM, BN, NT, WGM, WGN, TB>(ga_, (const GemmArgs*)__builtin_amdgcn_kernarg_segment_ptr(), vb);
+    gemm_split_kernel_body<BM, BN, NT, WGM, WGN, CALL, TB>(ga_, (const GemmArgs*)__builtin_amdgcn_kernarg_segment_ptr(), vb);
   } else {
     VBlock vb;
     const GemmArgs g = group_args(grp, bmap, vb);
     if (!slice_block(g, vb)) return;   // the instance's grid may be padded
-    gemm_split_kernel_body<BM, BN, NT, WGM, WGN, TB>(g, grp + bmap[blockIdx.x].x, vb);
+    gemm_split_kernel_body<BM, BN, NT, WGM, WGN, CALL, TB>(g, grp + bmap[blockIdx.x].x, vb);
   }
 }
 
@@ -1039,12 +1042,12 @@ static hipError_t launch_gemm_mn(dctk_ctx ctx, hipStream_t s, GemmArgs ga, int t
 #undef DCTK_GMN
 }
 
-template <int BM, int BN, int NT, int WGM, int WGN>
+template <int BM, int BN, int NT, int WGM, int WGN, int WAVES>
 static hipError_t launch_gemm_split(dctk_ctx ctx, hipStream_t s, GemmArgs ga, int tb, int batch) {
   ga.nbatch = batch >= kSliceXcdMin ? batch : 0;
   const int gz = ga.nbatch > 0 ? (batch + 7) / 8 * 8 : batch;
   const dim3 grid((unsigned)((ga.N + BN - 1) / BN), (unsigned)((ga.M + BM - 1) / BM), (unsigned)gz);
-#define DCTK_GSP(TB_) return launch_kernel(ctx, s, gemm_split_kernel<BM, BN, NT, WGM, WGN, TB_, false>, gemm_split_kernel<BM, BN, NT, WGM, WGN, TB_, true>, grid, NT, 0, ga)
+#define DCTK_GSP(TB_) return launch_kernel(ctx, s, gemm_split_kernel<BM, BN, NT, WGM, WGN, WAVES, TB_, false>, gemm_split_kernel<BM, BN, NT, WGM, WGN, WAVES, TB_, true>, grid, NT, 0, ga)
   if (tb) DCTK_GSP(true);
   DCTK_GSP(false);
 #undef DCTK_GSP
@@ -1104,11 +1107,16 @@ static hipError_t launch_gemm_vec(dctk_ctx ctx, hipStream_t s, int M, int N, int
     if (split_shape_ok(lda, ldb)) {
       const int best = split_tile(M, N, batch, num_cus);
       if ((tile == 128 || (tile == 0 && t64 >= (int64_t)num_cus)) && best == 256)
-        return launch_gemm_split<256, 256, 512, 2, 4>(ctx, s, ga, tb, batch);
+        return launch_gemm_split<256, 256, 512, 2, 4, 2>(ctx, s, ga, tb, batch);
       if (tile == 128 || (tile == 0 && t64 >= (int64_t)num_cus && best == 128))
-        return launch_gemm_split<128, 128, 256, 2, 2>(ctx, s, ga, tb, batch);
-      if (tile == 64 || (tile == 0 && t64 >= (int64_t)num_cus))
-        return launch_gemm_split<64, 64, 256, 2, 2>(ctx, s, ga, tb, batch);
+        return launch_gemm_split<128, 128, 256, 2, 2, 2>(ctx, s, ga, tb, batch);
+      if (tile == 64 || (tile == 0 && t64 >= (int64_t)num_cus)) {
+        // four workgroups a CU, or, where that saves a round, five in fewer registers (31 x 352^3: 32.4 us with
+        // four, 30.7 with five; where it saves none, 32 x 256^3: 16.4 and 17.3)
+        const int64_t r4 = (t64 + 4 * num_cus - 1) / (4 * num_cus), r5 = (t64 + 5 * num_cus - 1) / (5 * num_cus);
+        if (r5 < r4) return launch_gemm_split<64, 64, 256, 2, 2, 5>(ctx, s, ga, tb, batch);
+        return launch_gemm_split<64, 64, 256, 2, 2, 4>(ctx, s, ga, tb, batch);
+      }
     }
   }
   if (tile == 64 || tile == 128 || (tile == 0 && t64 >= (int64_t)num_cus))

@@ -636,6 +636,7 @@ __device__ __forceinline__ void tube_pair_kernel_body(const PairArgs& pa, const 
     g1[u] = ok ? v1 : 0.0f;
   }
   double a_d, b_d, s_d;
+  asm volatile("" ::"v"(alpha1));   // waited for with the control block's values, not on its own
   if (!ctl_eval(pa.ctl, cl, a_d, b_d, s_d, sh, vb)) return;
   const int ex = std::is_same<TX, f16_t>::value ? 0 : pair_exp(alpha1);
   const float xs = pow2f(-ex), b = (float)b_d;
@@ -763,6 +764,7 @@ __device__ __forceinline__ void tube_pair_small_body(const PairArgs& pa, const V
   const float g = pa.G1[gi < p * p ? gi : 0];
   load(e0);
   double a_d, b_d, s_d;
+  asm volatile("" ::"v"(alpha1));   // waited for with the control block's values, not on its own
   if (!ctl_eval(pa.ctl, cl, a_d, b_d, s_d, sh, vb)) return;
   const int ex = pair_exp(alpha1);
   const float xs = pow2f(-ex), b = has_src ? (float)b_d : 0.0f;
