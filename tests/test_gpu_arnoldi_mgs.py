@@ -1,5 +1,5 @@
-"""Arnoldi steps whose modified Gram-Schmidt coefficients come from the triangular system (I + L) h = r (L the
-strictly lower Gram triangle of the basis): vector lengths that are no multiple of 4 or of a workgroup, one to
+"""Arnoldi steps: FP32 modified Gram-Schmidt coefficients from the triangular system (I + L) h = r (L the strictly lower
+Gram triangle of the basis), FP64 ones term by term: vector lengths that are no multiple of 4 or of a workgroup, one to
 64 basis vectors (whole and partial groups of 8), both vector types, repeated cycles.
 
 FP64: H and the basis against the oracle's term-by-term MGS, 1e-9 relative (the tolerance of the other Arnoldi
