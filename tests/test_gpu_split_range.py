@@ -120,3 +120,22 @@ def test_largest_tile_both_contiguous_in_k(ctx, small):
         B = B * 2.0 ** 90
     Z, ref = product(ctx, A, B, R, 0, True), Operator(A, B).adjoint(R)
     assert np.linalg.norm(Z - ref) <= 1e-5 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("small", [False, True])
+def test_five_workgroups_per_cu(ctx, small):
+    """64 slices of 270 x 250 outputs: 1280 tiles of 64 x 64, one round of 256 CUs with five each, ragged both ways; the
+    product, and the right factor of a two-sided adjoint."""
+    from oracle.cprod import Operator
+    rng = np.random.default_rng(8)
+    A, X = rng.standard_normal((64, 270, 40)), f32(rng.standard_normal((64, 40, 250)))
+    if small:
+        A, X = A * 2.0 ** -118, f32(X * 2.0 ** 90)
+    Y, ref = product(ctx, A, None, X, 0, False), Operator(A).apply(X)
+    assert np.linalg.norm(Y - ref) <= 1e-5 * np.linalg.norm(ref)
+    A, B = rng.standard_normal((64, 24, 270)), rng.standard_normal((64, 250, 250))
+    R = f32(rng.standard_normal((64, 24, 250)))
+    if small:
+        A, R, B = A * 2.0 ** -60, f32(R * 2.0 ** -58), B * 2.0 ** 90
+    Z, ref = product(ctx, A, B, R, 0, True), Operator(A, B).adjoint(R)
+    assert np.linalg.norm(Z - ref) <= 1e-5 * np.linalg.norm(ref)
